@@ -1,0 +1,48 @@
+"""GPU parity where the tile kernels' selection can go wrong: equal depths inside and across the
+16 kept fragments, lists at the sizes between which the kernels change, parts of a tile that
+start inside a word of the kept bits; against the oracle with the tolerances of gpu_util."""
+import numpy as np
+import pytest
+
+import scenes
+from gpu_util import GRAD_KEY, PARAMS, assert_lists, assert_pyramid, grad_close, to_device
+from oracle import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(sc, dev, tuning=None, include_coarser=False, seed=0):
+    """Lists, colours and gradients of one view; returns the renderer."""
+    import torch
+    import paper_2401_06003_amd as tp
+    cam, nl, D = sc["cams"][0], sc["nlayers"], sc["D"]
+    r = tp.Renderer([cam], nl, D, len(sc["points"]["x"]), tuning=tuning, device=dev,
+                    include_coarser=include_coarser)
+    t = to_device(sc["points"], dev)
+    args = [t[k] for k in PARAMS]
+    out = r.forward(*args)
+    counts, ids = r.export_fragments()
+    P = r.texels
+    G = scenes.upstream_gradient(seed, P * D).reshape(P, D)
+    outs = r.backward(*args, torch.from_numpy(G.reshape(-1)).to(dev))
+    torch.cuda.synchronize()
+    f = oracle.forward_ex(sc["points"], cam, nl, coarser=include_coarser)
+    assert_lists(counts.cpu().numpy(), ids.cpu().numpy().astype(np.int64), f["counts"], f["ids"])
+    assert_pyramid(out.cpu().numpy().astype(np.float64).reshape(P, D), f["pyr"])
+    b = oracle.backward_ex(sc["points"], cam, nl, G.astype(np.float64), coarser=include_coarser)
+    for k, o in zip(PARAMS, outs):
+        g = o.cpu().numpy().astype(np.float64)
+        grad_close(g, b[GRAD_KEY[k]].reshape(g.shape), k)
+    return r
+
+
+@pytest.mark.parametrize("D,coarser,item,n", [(4, False, 0, 4000), (8, False, 300, 4000),
+                                              (4, True, 0, 1500), (4, False, 0, 700)])
+def test_equal_depths_in_the_lists(gpu, D, coarser, item, n):
+    """Four depths for all points: a texel's kept list holds equal depths, and the 16th kept
+    fragment has the depth of fragments that are not kept."""
+    import paper_2401_06003_amd as tp
+    sc = scenes.random_small(21, n=n, W=45, H=37, nlayers=4, D=D, s_lo=0.5, s_hi=14.0,
+                             depth_ties=True)
+    r = _check(sc, gpu, tp.make_tuning(16, 0, item), coarser)
+    assert r.tile_stats()[0].max() > 256
