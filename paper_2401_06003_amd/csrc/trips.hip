@@ -17,9 +17,9 @@
 //              entries -> fragments in LDS, counting sort by texel, per-texel top-16 kept
 //              in registers (thread = texel); blend, or write a partial top-16.
 //   fwd_merge  heavy bins: merge the partial top-16 lists, blend.
-//   bwd_pixels per texel: recompute T_m, reverse recurrence -> (dgamma_m, T_m gamma_m).
-//   bwd_items  per work item: every entry looks its corners up in the tile's kept lists
-//              (LDS) and writes one partial-gradient row per (view, slot, point).
+//   bwd_items  per work item: recompute T_m per texel, reverse recurrence -> (dgamma_m,
+//              T_m gamma_m) in LDS; every entry looks its corners up in the tile's kept
+//              lists and, if one is kept, writes one partial-gradient row.
 //   bwd_points per point: sum its rows, chain rule through the projection, write grads.
 // Every result is deterministic: ordering keys are unique (depth bits, point index) and
 // every sum is taken in a fixed order.
@@ -32,6 +32,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "trips.h"
@@ -51,7 +52,8 @@ constexpr uint64_t KEY_NONE = ~0ull;
 // per-slot adjoints that the inclusion pass accumulates).
 constexpr uint32_t FINE_E = 256;
 // The backward needs no merge, so its workgroups take smaller parts of the work items.
-constexpr uint32_t BWD_SPLIT = 2;
+constexpr uint32_t BWD_SPLIT = 2;    // with coarser-layer inclusion
+constexpr uint32_t BWD_GRID = 2048;  // else: workgroups of a launch, at most
 // Workgroups are dealt to the chip's 8 dies (XCDs, each with its own L2) in turn by index;
 // kernels that share data between workgroups place them 8 indices apart.  The work-item
 // capacity is a multiple of it.
@@ -406,8 +408,8 @@ __global__ __launch_bounds__(BIN_THREADS) void k_count(const Params P, const flo
 
 // The tile scan over chunks of 64 tiles (one wavefront each): the chunk sums (written by the
 // column scan, whose workgroups cover the same chunks), then two short passes.  A tile
-// of at most FINE_E entries is listed in fine_work; every other tile is listed in coarse_bins
-// and cut into ceil(total / item_e) work items; tiles with more than one item are listed in
+// of at most FINE_E entries is listed in fine_work; every other tile is cut
+// into ceil(total / item_e) work items; tiles with more than one item are listed in
 // multi_bins (their partial lists are merged), with the first of their items' consecutive
 // partial-list slots NB words further on.  bin_start and item_start are the exclusive scans
 // of entries and items.
@@ -589,7 +591,6 @@ __global__ __launch_bounds__(1024) void k_chunkscan(const uint32_t* __restrict__
     info[2] = 0;  // visible (point, view) pairs, accumulated by the scatter pass
     info[3] = carry.z;
     info[4] = carry.w;
-    info[5] = NB - carry.w;
     uint32_t o = 0;
     for (int q = 0; q < NBUCKET; ++q) {  // first work slot of each size class; fill counters
       info[INFO_BUCKET + q] = o;
@@ -617,7 +618,6 @@ __global__ __launch_bounds__(64) void k_binscan(const uint32_t* __restrict__ tot
                                                 uint32_t* __restrict__ item_start,
                                                 uint32_t* __restrict__ multi_bins,
                                                 uint4* __restrict__ fine_work,
-                                                uint32_t* __restrict__ coarse_bins,
                                                 uint32_t* __restrict__ info, uint4* __restrict__ work,
                                                 uint32_t NB, uint32_t nch, uint32_t item_e,
                                                 uint32_t fine_e) {
@@ -667,7 +667,6 @@ __global__ __launch_bounds__(64) void k_binscan(const uint32_t* __restrict__ tot
       info[2] = 0;  // visible (point, view) pairs, accumulated by the scatter pass
       info[3] = all[2];
       info[4] = all[3];
-      info[5] = NB - all[3];
     }
   } else {
     const uint32_t* cp = coff + size_t(blockIdx.x) * 4;
@@ -686,7 +685,6 @@ __global__ __launch_bounds__(64) void k_binscan(const uint32_t* __restrict__ tot
       multi_bins[NB + om] = oi - (b - om - of);
     }
     if (c.fine) fine_work[of] = make_uint4(b, oe, oe + c.e, 0u);
-    else coarse_bins[b - of] = b;  // tiles before b that are not fine
   }
   // work items: consecutive ranges of item_e entries (the last holds the rest), all in the
   // class of the tile's average item (the forward takes them as strided blocks)
@@ -1514,88 +1512,11 @@ __device__ __forceinline__ float2 blend_adjoint_step(float Tm, float gam, float 
   return make_float2(dgam, Tm * gam);
 }
 
-// bwd_pixels: per texel, recompute transmittance T_m front to back and run the reverse
-// recurrence B_{m-1} = gamma_m g_m + (1 - gamma_m) B_m (g_m = G . tau_m, B_last = 0):
-// dL/dgamma_m = T_m (g_m - B_m); the descriptor gets T_m gamma_m G.
-template <int D>
-__global__ __launch_bounds__(256) void k_bwd_pixels(const Params P, const uint32_t* __restrict__ info,
-                                                    const uint32_t* __restrict__ coarse_bins,
-                                                    const uint32_t* __restrict__ npix,
-                                                    const uint64_t* __restrict__ kkey,
-                                                    const float* __restrict__ kgam,
-                                                    const float* __restrict__ desc,
-                                                    const float* __restrict__ gpyr,
-                                                    float2* __restrict__ bst, const Extras X) {
-  const int t = threadIdx.x;
-  const uint32_t b = coarse_bins[blockIdx.x];  // in bounds (grid = bin count); used if valid
-  if (blockIdx.x >= info[5]) return;
-  const uint32_t n = npix[size_t(b) * TP + t];
-  if (n == 0 && !X.gbg) return;
-  const BinInfo bi = decode_bin(P, b);
-  const int lth = 8 - P.ltw;
-  const int i = (bi.tx << P.ltw) + (t & ((1 << P.ltw) - 1));
-  const int j = (bi.ty << lth) + (t >> P.ltw);
-  if (!(i < bi.WL && j < bi.HL)) return;  // (such texels hold no fragments)
-  const size_t tex = size_t(P.view[bi.v].lout[bi.L]) + size_t(j) * bi.WL + i;
-  const size_t o = tex * D;
-  float G[D];
-  const float4* gp = reinterpret_cast<const float4*>(gpyr + o);
-#pragma unroll
-  for (int q = 0; q < D / 4; ++q) {
-    float4 gv = gp[q];
-    G[4 * q] = gv.x; G[4 * q + 1] = gv.y; G[4 * q + 2] = gv.z; G[4 * q + 3] = gv.w;
-  }
-  if (n == 0) {  // only the background shows
-    float4* gb = reinterpret_cast<float4*>(X.gbg + o);
-#pragma unroll
-    for (int q = 0; q < D / 4; ++q) gb[q] = make_float4(G[4 * q], G[4 * q + 1], G[4 * q + 2], G[4 * q + 3]);
-    return;
-  }
-  const uint32_t k = min(n, uint32_t(KEEP));
-  float gam[KEEP], Tm[KEEP], gm[KEEP];
-  uint32_t idx[KEEP];
-  // kept entries first (independent loads), then the descriptor gathers in batches
-#pragma unroll
-  for (int m = 0; m < KEEP; ++m) {
-    const size_t ko = (size_t(b) * KEEP + m) * TP + t;
-    const bool v = uint32_t(m) < k;
-    idx[m] = v ? uint32_t(kkey[ko]) : 0u;
-    gam[m] = v ? kgam[ko] : 0.0f;
-  }
-  float T = 1.0f;
-#pragma unroll
-  for (int m = 0; m < KEEP; ++m) {
-    Tm[m] = T;
-    if (uint32_t(m) < k) T = T * (1.0f - gam[m]);
-  }
-  constexpr int GB = D > 4 ? 4 : 8;
-#pragma unroll
-  for (int m0 = 0; m0 < KEEP; m0 += GB) {
-    float4 tv[GB][D / 4];
-#pragma unroll
-    for (int q = 0; q < GB; ++q) {
-      const float4* tp = reinterpret_cast<const float4*>(desc + size_t(idx[m0 + q]) * D);
-#pragma unroll
-      for (int r = 0; r < D / 4; ++r)
-        tv[q][r] = uint32_t(m0 + q) < k ? tp[r] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int q = 0; q < GB; ++q) gm[m0 + q] = dot_g<D>(G, tv[q]);
-  }
-  if (X.galpha) {  // the coverage blends a constant 1 through the same weights
-    const float ga = X.galpha[tex];
-#pragma unroll
-    for (int m = 0; m < KEEP; ++m) gm[m] += ga;
-  }
-  float B = X.bg ? dot_g<D>(G, *reinterpret_cast<const float4(*)[D / 4]>(X.bg + o)) : 0.0f;
-#pragma unroll
-  for (int m = KEEP - 1; m >= 0; --m)
-    if (uint32_t(m) < k) bst[(size_t(b) * KEEP + m) * TP + t] = blend_adjoint_step(Tm[m], gam[m], gm[m], B);
-  if (X.gbg) write_scaled<D>(X.gbg + o, T, G);
-}
-
-// bwd_items: per work item, each entry finds its corners in the tile's kept lists and writes
-// its partial-gradient row: (A, Bx, By, 0, tau[D]) with A = sum dgamma wx wy,
+// bwd_items: per work item, first the blend adjoint of the tile's texels: transmittance T_m front
+// to back, then the reverse recurrence B_{m-1} = gamma_m g_m + (1 - gamma_m) B_m (g_m = G . tau_m,
+// B_last = 0 or the background's): dL/dgamma_m = T_m (g_m - B_m), the descriptor gets T_m gamma_m G.
+// Two threads per texel share its list and hand T and B on through LDS, where the results stay.
+// Then each entry finds its corners in the tile's kept lists and writes its partial-gradient row: (A, Bx, By, 0, tau[D]) with A = sum dgamma wx wy,
 // Bx = sum dgamma sx wy, By = sum dgamma wx sy, tau = sum T_m gamma_m G over its corners.
 // The lists are in depth order, so a corner's slot is found by bisection of the texel's 16
 // depths in LDS (five reads instead of a comparison with all 16 point ids).  A fragment as deep
@@ -1604,99 +1525,173 @@ __global__ __launch_bounds__(256) void k_bwd_pixels(const Params P, const uint32
 // With coarser-layer inclusion (INC) the kept own fragments are those the blended list took
 // (a prefix of the own list), and each one's totals (dL/dgamma, tau part) are read from
 // itot instead of being formed from the blend adjoint and G.
-// Bound by memory traffic and by the wavefronts in flight.  The bisection and the rows left
-// out took it from 89 to 77 us at 2M points, 252 to 210 us at 8M (1920x1080, D = 4) and 2.74 to
-// 1.80 ms on eight 2560x1440 views (8M points, D = 8), where two thirds of the entries keep
-// nothing.
-template <int D, bool INC>
-__global__ __launch_bounds__(256) void k_bwd_items(
+// Bound by the latency of its gathers and the wavefronts in flight (57 KB of LDS: two workgroups
+// of 512 threads per CU).  The adjoint used to be a kernel of its own that passed (dL/dgamma,
+// T gamma) through memory; at 1920x1080, D = 4, the two took 49 + 89 us at 2M points and 141 +
+// 252 us at 8M; bisecting the depths and leaving rows out made the second 77 and 210 us, and one
+// kernel of both takes 115 and 295 us.
+template <int D, bool INC, int T>
+__global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
     const Params P, const uint32_t* __restrict__ info, const uint4* __restrict__ work,
-    const uint32_t* __restrict__ bin_start, const uint32_t* __restrict__ item_start,
-    const Entry* __restrict__ ent,
+    const uint32_t* __restrict__ bin_start, const Entry* __restrict__ ent,
     const uint32_t* __restrict__ npix, const uint64_t* __restrict__ kkey,
-    const float2* __restrict__ bst, const float* __restrict__ gpyr, float* __restrict__ rows,
-    unsigned long long* __restrict__ kept, uint32_t split, const uint32_t* __restrict__ fcnt,
-    const float* __restrict__ itot) {
+    const float* __restrict__ kgam, const float* __restrict__ desc,
+    const float* __restrict__ gpyr, float* __restrict__ rows,
+    unsigned long long* __restrict__ kept, const uint32_t* __restrict__ fcnt,
+    const float* __restrict__ itot, const Extras X) {
   constexpr int RW = 4 + D;
   constexpr int S = D + 1;
-  constexpr int EB = 3;  // entries per thread in flight
+  constexpr int EB = INC ? 3 : 2;  // entries per thread in flight
+  constexpr int H = T / TP, LQ = KEEP / H;  // threads per texel, list slots of each
+  static_assert(H <= 2, "T and B are handed on once");
   constexpr uint32_t TIE = 0x80000000u;  // (depth bits of kept fragments are below it)
   __shared__ uint32_t s_z[KEEP][TP];   // depths of the kept fragments, ~0 past the list
   __shared__ uint2 s_last[TP];         // the last kept depth, with TIE if the list holds equal
                                        // ones, and its point index
-  __shared__ float s_G[TP][D + 1];
+  __shared__ float s_G[INC ? 1 : TP][D + 1];
+  __shared__ float2 s_bst[INC ? 1 : KEEP][INC ? 1 : TP];  // (dL/dgamma, T gamma) of the kept
+  __shared__ float s_hand[INC ? 1 : TP];
   const int t = threadIdx.x;
   const uint32_t total = info[1];
-  // every work item is shared by `split` workgroups, each taking an equal part of its entries;
-  // the parts of an item are XCDS indices apart (the same die, so the tile's lists and blend
-  // adjoints are fetched into one L2): workgroup g XCDS split + XCDS p + q takes part p of
-  // item g XCDS + q
-  const uint32_t grp = blockIdx.x / (XCDS * split), rem = blockIdx.x % (XCDS * split);
-  const uint32_t wi = grp * XCDS + rem % XCDS, part = rem / XCDS;
-  const uint4 wk = work[wi];  // in bounds (grid = split x capacity); used only if valid
-  if (wi >= total) return;
+  // With inclusion every work item is shared by BWD_SPLIT workgroups, each taking an equal part
+  // of its entries, XCDS indices apart (on the same die, so the tile's lists are fetched into one
+  // L2): workgroup g XCDS BWD_SPLIT + XCDS p + q takes part p of item g XCDS + q.  Without, a
+  // workgroup takes whole items, strided over the grid.
+  constexpr uint32_t NP = INC ? BWD_SPLIT : 1;
+  for (uint32_t wi = INC ? blockIdx.x / (XCDS * NP) * XCDS + blockIdx.x % XCDS : blockIdx.x; wi < total;
+       wi += gridDim.x) {
+  const uint32_t part = INC ? blockIdx.x % (XCDS * NP) / XCDS : 0u;
+  const uint4 wk = work[wi];
   const uint32_t b = wk.x;
-  // the tile's entries t0..t1 in equal parts
-  uint32_t t0 = wk.y, t1 = wk.z, pi = part, np = split;
-  if (wk.w >> 31) {
-    t0 = bin_start[b];
-    t1 = bin_start[b + 1];
-    pi += (wk.y - t0) / P.item_e * split;
-    np *= item_start[b + 1] - item_start[b];
-  }
-  const uint32_t chunk = (t1 - t0 + np - 1) / np;
-  const uint32_t e0 = t0 + min(t1 - t0, pi * chunk);
-  const uint32_t e1 = t0 + min(t1 - t0, (pi + 1) * chunk);
-  if (e0 == e1) return;
+  const uint32_t chunk = (wk.z - wk.y + NP - 1) / NP;
+  const uint32_t e0 = wk.y + min(wk.z - wk.y, part * chunk);
+  const uint32_t e1 = wk.y + min(wk.z - wk.y, (part + 1) * chunk);
+  if (INC && e0 == e1) return;
   // the first entries of this thread, loaded while the tile is staged
   Entry nx[EB];
 #pragma unroll
   for (int q = 0; q < EB; ++q)
-    if (e0 + q * TP + t < e1) nx[q] = ent[e0 + q * TP + t];
+    if (e0 + q * T + t < e1) nx[q] = ent[e0 + q * T + t];
   const BinInfo bi = decode_bin(P, b);
   const TileGeo tg = tile_geo(bi, P.ltw);
-  {  // stage the tile's kept depths and upstream gradient
-    const uint32_t k = INC ? (fcnt[size_t(b) * TP + t] & 31u) : min(npix[size_t(b) * TP + t], uint32_t(KEEP));
-    uint64_t raw[KEEP];
-    // all 16 loads are issued together: slots past the list read slot 0 of the same texel
-    // (a valid address) and are discarded
+  // the tile's kept depths and, without inclusion, its blend adjoints
+  {
+    const int x = t & (TP - 1), h = t / TP;
+    const uint32_t n = npix[size_t(b) * TP + x];
+    const uint32_t k = INC ? (fcnt[size_t(b) * TP + x] & 31u) : min(n, uint32_t(KEEP));
+    uint64_t raw[LQ];
+    float gam[LQ];
+    // all loads are issued together: slots past the list read slot 0 of the same texel (a valid
+    // address) and are discarded
 #pragma unroll
-    for (int m = 0; m < KEEP; ++m)
-      raw[m] = kkey[(size_t(b) * KEEP + (uint32_t(m) < k ? m : 0)) * TP + t];
-    uint64_t last = KEY_NONE;
-    bool tie = false;
-#pragma unroll
-    for (int m = 0; m < KEEP; ++m) {
-      const bool v = uint32_t(m) < k;
-      tie |= v && uint32_t(raw[m] >> 32) == uint32_t(last >> 32);
-      last = v ? raw[m] : last;
-      s_z[m][t] = v ? uint32_t(raw[m] >> 32) : ~0u;
+    for (int q = 0; q < LQ; ++q) {
+      const size_t o = (size_t(b) * KEEP + (uint32_t(LQ * h + q) < k ? LQ * h + q : 0)) * TP + x;
+      raw[q] = kkey[o];
+      if (!INC) gam[q] = kgam[o];
     }
-    s_last[t] = make_uint2(uint32_t(last >> 32) | (tie ? TIE : 0u), uint32_t(last));
-    const int i = tg.x0 + (t & ((1 << P.ltw) - 1));
-    const int j = tg.y0 + (t >> P.ltw);
-    if (!INC && k > 0) {  // texels with fragments lie inside the layer
-      const size_t o = (size_t(P.view[bi.v].lout[bi.L]) + size_t(j) * bi.WL + i) * D;
+    const int i = tg.x0 + (x & ((1 << P.ltw) - 1)), j = tg.y0 + (x >> P.ltw);
+    const bool in = i < bi.WL && j < bi.HL;  // (texels with fragments are)
+    // (of a tile cut into items, the item with the tile's first entry writes the background)
+    const bool first_part = !(wk.w >> 31) || e0 == bin_start[b];
+    const size_t tex = size_t(P.view[bi.v].lout[bi.L]) + size_t(in ? j : 0) * bi.WL + (in ? i : 0);
+    float G[D];
+    if (!INC) {
+      const float4* gp = reinterpret_cast<const float4*>(gpyr + tex * D);
 #pragma unroll
-      for (int d = 0; d < D; ++d) s_G[t][d] = gpyr[o + d];
+      for (int q = 0; q < D / 4; ++q) {
+        const float4 gv = gp[q];
+        G[4 * q] = gv.x; G[4 * q + 1] = gv.y; G[4 * q + 2] = gv.z; G[4 * q + 3] = gv.w;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < LQ; ++q) s_z[LQ * h + q][x] = uint32_t(LQ * h + q) < k ? uint32_t(raw[q] >> 32) : ~0u;
+    if (!INC) {
+      if (h == 0) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) s_G[x][d] = G[d];
+      }
+      float gm[LQ], Tm[LQ];
+      constexpr int GB = D > 4 ? 4 : 8;  // descriptor gathers in flight
+#pragma unroll
+      for (int m0 = 0; m0 < LQ; m0 += GB) {
+        float4 tv[GB][D / 4];
+#pragma unroll
+        for (int q = 0; q < GB; ++q) {
+          const float4* tp = reinterpret_cast<const float4*>(desc + size_t(uint32_t(raw[m0 + q])) * D);
+#pragma unroll
+          for (int r = 0; r < D / 4; ++r)
+            tv[q][r] = uint32_t(LQ * h + m0 + q) < k ? tp[r] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int q = 0; q < GB; ++q) gm[m0 + q] = dot_g<D>(G, tv[q]);
+      }
+      if (X.galpha) {  // the coverage blends a constant 1 through the same weights
+        const float ga = X.galpha[tex];
+#pragma unroll
+        for (int q = 0; q < LQ; ++q) gm[q] += ga;
+      }
+      float Tr = 1.0f;
+      auto front = [&]() {
+#pragma unroll
+        for (int q = 0; q < LQ; ++q) {
+          Tm[q] = Tr;
+          if (uint32_t(LQ * h + q) < k) Tr = Tr * (1.0f - gam[q]);
+        }
+      };
+      auto back = [&](float B) {
+#pragma unroll
+        for (int q = LQ - 1; q >= 0; --q)
+          if (uint32_t(LQ * h + q) < k)
+            s_bst[LQ * h + q][x] = blend_adjoint_step(Tm[q], gam[q], gm[q], B);
+        return B;
+      };
+      if (h == 0) {
+        front();
+        s_hand[x] = Tr;
+      }
+      __syncthreads();
+      if (h == 1) {
+        Tr = s_hand[x];
+        front();
+        const float B = X.bg ? dot_g<D>(G, *reinterpret_cast<const float4(*)[D / 4]>(X.bg + tex * D)) : 0.0f;
+        s_hand[x] = back(B);
+        if (X.gbg && in && first_part) write_scaled<D>(X.gbg + tex * D, Tr, G);  // (the first part)
+      }
+      __syncthreads();
+      if (h == 0) back(s_hand[x]);
+    } else {
+      __syncthreads();
+    }
+    // the last kept fragment, and whether the list holds equal depths
+    if (h == 0) {
+      uint32_t last = ~0u, id = ~0u;
+      bool tie = false;
+#pragma unroll
+      for (int m = 0; m < KEEP; ++m) {
+        const uint32_t z = s_z[m][x];
+        tie |= uint32_t(m) < k && z == last;
+        last = uint32_t(m) < k ? z : last;
+      }
+      if (k > 0) id = uint32_t(kkey[(size_t(b) * KEEP + (k - 1)) * TP + x]);
+      s_last[x] = make_uint2(last | (tie ? TIE : 0u), id);
     }
   }
   __syncthreads();
-  for (uint32_t e = e0 + t; e - (t & 63) < e1; e += EB * TP) {  // (whole wavefronts)
+  for (uint32_t e = e0 + t; e - (t & 63) < e1; e += EB * T) {  // (whole wavefronts)
     Entry en[EB];
 #pragma unroll
     for (int q = 0; q < EB; ++q) {
       en[q] = nx[q];
-      if (e + (EB + q) * TP < e1) nx[q] = ent[e + (EB + q) * TP];  // next round of entries
+      if (e + (EB + q) * T < e1) nx[q] = ent[e + (EB + q) * T];  // next round of entries
     }
-    // find the kept slot of every corner, then gather the blend adjoints of all of them
+    // find the kept slot of every corner, then the adjoints of all of them
     int p0[EB];
     float fu[EB], fv[EB];
     uint32_t cm[EB];
-    size_t pos[EB][4];
+    typename std::conditional<INC, size_t, uint32_t>::type pos[EB][4];
 #pragma unroll
     for (int h = 0; h < EB; ++h) {
-      const int pm = e + h * TP < e1 ? tile_corners(tg, en[h].u, en[h].v, fu[h], fv[h]) : 0;
+      const int pm = e + h * T < e1 ? tile_corners(tg, en[h].u, en[h].v, fu[h], fv[h]) : 0;
       p0[h] = pm >> 4;
       cm[h] = uint32_t(pm) & 15u;
       const uint32_t z = en[h].zbits;
@@ -1719,8 +1714,7 @@ __global__ __launch_bounds__(256) void k_bwd_items(
         }
         cm[h] &= on ? ~0u : ~(1u << q);
         pos[h][q] = !on ? 0
-                    : INC ? (size_t(b) * KEEP + m) * S * TP + p
-                          : (size_t(b) * KEEP + m) * TP + p;
+                    : INC ? (size_t(b) * KEEP + m) * S * TP + p : m * TP + p;
       }
     }
     float2 st[EB][4];
@@ -1736,12 +1730,12 @@ __global__ __launch_bounds__(256) void k_bwd_items(
           for (int d = 0; d < D; ++d)
             itau[INC ? h : 0][q][INC ? d : 0] = on ? itot[pos[h][q] + size_t(1 + d) * TP] : 0.0f;
         } else {
-          st[h][q] = on ? bst[pos[h][q]] : make_float2(0.f, 0.f);
+          st[h][q] = on ? s_bst[INC ? 0 : pos[h][q] / TP][INC ? 0 : pos[h][q] % TP] : make_float2(0.f, 0.f);
         }
       }
 #pragma unroll
     for (int h = 0; h < EB; ++h) {
-      const uint32_t eh = e + h * TP;
+      const uint32_t eh = e + h * T;
       const uint64_t bits = __ballot(cm[h] != 0);
       if ((t & 63) == 0) mark_kept(kept, eh, bits);
       if (cm[h] == 0) continue;
@@ -1760,7 +1754,7 @@ __global__ __launch_bounds__(256) void k_bwd_items(
         Bx += dg * (sx * wy);
         By += dg * (wx * sy);
 #pragma unroll
-        for (int d = 0; d < D; ++d) tau[d] += INC ? itau[INC ? h : 0][q][INC ? d : 0] : st[h][q].y * s_G[p][d];
+        for (int d = 0; d < D; ++d) tau[d] += INC ? itau[INC ? h : 0][q][INC ? d : 0] : st[h][q].y * s_G[INC ? 0 : p][d];
       }
       float* r = rows + size_t(eh) * RW;  // rows in entry order
       float4* r4 = reinterpret_cast<float4*>(r);
@@ -1770,12 +1764,15 @@ __global__ __launch_bounds__(256) void k_bwd_items(
         r4[1 + q] = make_float4(tau[4 * q], tau[4 * q + 1], tau[4 * q + 2], tau[4 * q + 3]);
     }
   }
+  if (INC) return;
+  __syncthreads();  // the next item may overwrite the lists
+  }
 }
 
 // bwd_fine: the backward of fine tiles, one workgroup per tile and one entry per thread.
 // The kept slot of every corner was recorded by the forward pass, so the kept lists are
 // rebuilt in LDS from the entries themselves (compact: texel t's list starts at s_off[t]);
-// each texel's thread runs the blend adjoint (as bwd_pixels does) and every entry then
+// each texel's thread runs the blend adjoint (as bwd_items does) and every entry then
 // writes its row (as bwd_items does).
 template <int D>
 __global__ __launch_bounds__(256) void k_bwd_fine(
@@ -1858,7 +1855,7 @@ __global__ __launch_bounds__(256) void k_bwd_fine(
     }
   }
   __syncthreads();
-  if (inl && (k > 0 || X.gbg)) {  // blend adjoint of texel t (as in bwd_pixels)
+  if (inl && (k > 0 || X.gbg)) {  // blend adjoint of texel t (as in bwd_items)
     const uint32_t o0 = s_off[t];
     float G[D];
 #pragma unroll
@@ -2373,7 +2370,7 @@ __device__ __forceinline__ uint32_t blended_adjoint(const BlendedSrc& S, uint32_
 
 // incl_bwd: one launch per layer, finest first; four threads per texel, a quarter of a tile
 // (64 texels) per workgroup (grid.x = 4 x the layer's tiles, grid.y = view).  All four
-// threads of a texel run the blend adjoint of its blended list (as bwd_pixels; their loads
+// threads of a texel run the blend adjoint of its blended list (as bwd_items; their loads
 // are the same addresses, merged by the memory system), which gives every item dL/dgamma
 // and T gamma G; thread g then completes items g, g + 4, g + 8 and g + 12: the blend part,
 // then what each of the four finer texels the texel covers passed up for the item, in
@@ -3063,11 +3060,11 @@ struct Layout {
   uint64_t icap;      // work-item capacity
   uint64_t npyr;      // texels of all views and layers
   // saved buffer
-  size_t s_info, s_bin_start, s_item_start, s_multi, s_fine, s_coarse, s_npix, s_kkey, s_kgam,
+  size_t s_info, s_bin_start, s_item_start, s_multi, s_fine, s_npix, s_kkey, s_kgam,
       s_fkey, s_fgam, s_fcnt, s_kslot, s_tables_end, s_work, s_ent, s_epos, s_kept;
   size_t saved_bytes;
   // workspace
-  size_t w_H16, w_H, w_tot, w_csum, w_coff, w_pcnt, w_pkey, w_pgam, w_bst, w_rows, w_cam, w_itot, w_iup,
+  size_t w_H16, w_H, w_tot, w_csum, w_coff, w_pcnt, w_pkey, w_pgam, w_rows, w_cam, w_itot, w_iup,
       ws_bytes;
   size_t ws_fwd_bytes;  // the part of the workspace a forward call uses
 };
@@ -3168,7 +3165,6 @@ trips_status make_layout(const trips_config* cfg, const trips_camera* cams, int3
   lay.s_item_start = take((NB + 1) * 4);
   lay.s_multi = take(2 * NB * 4);
   lay.s_fine = take(NB * sizeof(uint4));
-  lay.s_coarse = take(NB * 4);
   // texel tables: their offsets depend only on the cameras and config (export reads them)
   lay.s_npix = take(NB * TP * 4);
   lay.s_kkey = take(NB * TP * KEEP * 8);
@@ -3204,7 +3200,6 @@ trips_status make_layout(const trips_config* cfg, const trips_camera* cams, int3
   const size_t fwd_end = o;
   // backward scratch reuses the same bytes
   o = scratch;
-  lay.w_bst = take(NB * TP * KEEP * sizeof(float2));
   lay.w_rows = take(size_t(views) * NSLOT * size_t(n) * (4 + P.D) * 4);
   lay.w_cam = take(size_t((n + 255) / 256) * size_t(views) * 16 * 4);
   lay.w_itot = take(inc * NB * TP * KEEP * size_t(1 + P.D) * 4);
@@ -3341,7 +3336,6 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
   uint4* work = reinterpret_cast<uint4*>(sv + lay.s_work);
   uint32_t* multi_bins = reinterpret_cast<uint32_t*>(sv + lay.s_multi);
   uint4* fine_work = reinterpret_cast<uint4*>(sv + lay.s_fine);
-  uint32_t* coarse_bins = reinterpret_cast<uint32_t*>(sv + lay.s_coarse);
   uint32_t* npix = reinterpret_cast<uint32_t*>(sv + lay.s_npix);
   uint64_t* kkey = reinterpret_cast<uint64_t*>(sv + lay.s_kkey);
   float* kgam = reinterpret_cast<float*>(sv + lay.s_kgam);
@@ -3372,13 +3366,13 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
     StageTimer tm(ST_BINSCAN, st);
     if (nch <= FUSE_CHUNKS) {
       hipLaunchKernelGGL(k_binscan<true>, dim3(nch), dim3(CHUNK), 0, st, tot, csum, coff,
-                         bin_start, item_start, multi_bins, fine_work, coarse_bins, info, work,
+                         bin_start, item_start, multi_bins, fine_work, info, work,
                          P.NB, nch, P.item_e, P.fine_e);
     } else {
       hipLaunchKernelGGL(k_chunkscan, dim3(1), dim3(1024), 0, st, csum, coff, bin_start,
                          item_start, info, P.NB, nch);
       hipLaunchKernelGGL(k_binscan<false>, dim3(nch), dim3(CHUNK), 0, st, tot, csum, coff,
-                         bin_start, item_start, multi_bins, fine_work, coarse_bins, info, work,
+                         bin_start, item_start, multi_bins, fine_work, info, work,
                          P.NB, nch, P.item_e, P.fine_e);
     }
   }
@@ -3465,7 +3459,6 @@ trips_status launch_backward(const Layout& lay, const trips_points& pts, const f
                              char* sv, char* ws, float* gx, float* gy, float* gz, float* gsw,
                              float* ga, float* gd, const Extras& X, hipStream_t st) {
   const Params& P = lay.P;
-  float2* bst = reinterpret_cast<float2*>(ws + lay.w_bst);
   float* rows = reinterpret_cast<float*>(ws + lay.w_rows);
   unsigned long long* kept = reinterpret_cast<unsigned long long*>(sv + lay.s_kept);
   const uint32_t* bin_start = reinterpret_cast<const uint32_t*>(sv + lay.s_bin_start);
@@ -3473,7 +3466,6 @@ trips_status launch_backward(const Layout& lay, const trips_points& pts, const f
   const uint32_t* info = reinterpret_cast<const uint32_t*>(sv + lay.s_info);
   const uint4* work = reinterpret_cast<const uint4*>(sv + lay.s_work);
   const uint4* fine_work = reinterpret_cast<const uint4*>(sv + lay.s_fine);
-  const uint32_t* coarse_bins = reinterpret_cast<const uint32_t*>(sv + lay.s_coarse);
   const uint32_t* npix = reinterpret_cast<const uint32_t*>(sv + lay.s_npix);
   const uint64_t* kkey = reinterpret_cast<const uint64_t*>(sv + lay.s_kkey);
   const float* kgam = reinterpret_cast<const float*>(sv + lay.s_kgam);
@@ -3520,9 +3512,9 @@ trips_status launch_backward(const Layout& lay, const trips_points& pts, const f
     }
     {
       StageTimer tm(ST_BWD_ITEMS, st);
-      hipLaunchKernelGGL((k_bwd_items<D, true>), dim3(uint32_t(lay.icap) * BWD_SPLIT), dim3(256),
-                         0, st, P, info, work, bin_start, item_start, ent, npix, kkey, bst, gpyr, rows,
-                         kept, BWD_SPLIT, fcnt, itot);
+      hipLaunchKernelGGL((k_bwd_items<D, true, TP>), dim3(uint32_t(lay.icap) * BWD_SPLIT), dim3(TP),
+                         0, st, P, info, work, bin_start, ent, npix, kkey, kgam, pts.desc, gpyr, rows,
+                         kept, fcnt, itot, X);
     }
     TRIPS_HIP(hipGetLastError());
   } else {
@@ -3533,9 +3525,11 @@ trips_status launch_backward(const Layout& lay, const trips_points& pts, const f
     std::lock_guard<std::mutex> lk(g_side_launch);
     TRIPS_HIP(hipEventRecord(sd->fork, st));
     {  // the longer path first
-      StageTimer tm(ST_BWD_PIXELS, st);
-      hipLaunchKernelGGL(k_bwd_pixels<D>, dim3(P.NB), dim3(256), 0, st, P, info, coarse_bins, npix,
-                         kkey, kgam, pts.desc, gpyr, bst, X);
+      StageTimer tm(ST_BWD_ITEMS, st);
+      hipLaunchKernelGGL((k_bwd_items<D, false, 512>),
+                         dim3(std::min<uint32_t>(uint32_t(lay.icap), BWD_GRID)), dim3(512), 0, st, P,
+                         info, work, bin_start, ent, npix, kkey, kgam, pts.desc, gpyr, rows, kept,
+                         nullptr, nullptr, X);
     }
     hipError_t e3 = hipGetLastError();
     hipError_t e0 = hipStreamWaitEvent(sd->s, sd->fork, 0);
@@ -3546,19 +3540,11 @@ trips_status launch_backward(const Layout& lay, const trips_points& pts, const f
     }
     hipError_t e1 = hipGetLastError();
     hipError_t e2 = hipEventRecord(sd->join, sd->s);
-    {
-      StageTimer tm(ST_BWD_ITEMS, st);
-      hipLaunchKernelGGL((k_bwd_items<D, false>), dim3(uint32_t(lay.icap) * BWD_SPLIT), dim3(256),
-                         0, st, P, info, work, bin_start, item_start, ent, npix, kkey, bst, gpyr, rows,
-                         kept, BWD_SPLIT, nullptr, nullptr);
-    }
-    hipError_t e4 = hipGetLastError();
     TRIPS_HIP(hipStreamWaitEvent(st, sd->join, 0));
     TRIPS_HIP(e0);
     TRIPS_HIP(e1);
     TRIPS_HIP(e2);
     TRIPS_HIP(e3);
-    TRIPS_HIP(e4);
   }
   if (P.n > 0) {
     StageTimer tm(ST_BWD_POINTS, st);
