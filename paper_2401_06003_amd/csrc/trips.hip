@@ -804,6 +804,137 @@ __global__ __launch_bounds__(BIN_THREADS) void k_scatter(const Params P, const f
   if (threadIdx.x == 0) atomicAdd(&info[2], s_vis);
 }
 
+// front: the whole binning (count, scans, scatter) of at most FRONT_N points in one view, by one
+// workgroup: its histogram is the tile totals, so no matrix and no scan over blocks is needed,
+// and the tables of count, binscan and scatter come out the same.  For so few points the four
+// launches are latency and one busy CU each; here every thread projects its points once and
+// keeps their entries (tile, place in the tile, footprint) in registers until the tiles'
+// starts are known.
+// Bound by one CU's instruction issue: 4096 points, 256x256: 29 us, for 43 us of the four
+// kernels and three gaps; 300 points 12 us.
+constexpr uint32_t FRONT_T = 1024;
+constexpr int FRONT_P = 4;  // points per thread
+constexpr uint32_t FRONT_N = FRONT_T * FRONT_P;
+__global__ __launch_bounds__(FRONT_T) void k_front(
+    const Params P, const float* __restrict__ X, const float* __restrict__ Y,
+    const float* __restrict__ Z, const float* __restrict__ SW, const float* __restrict__ A,
+    uint32_t* __restrict__ bin_start, uint32_t* __restrict__ item_start,
+    uint32_t* __restrict__ multi_bins, uint4* __restrict__ fine_work, uint32_t* __restrict__ info,
+    uint4* __restrict__ work, Entry* __restrict__ ent, uint32_t* __restrict__ epos,
+    uint64_t* __restrict__ kept) {
+  extern __shared__ uint32_t lds[];
+  __shared__ uint4 s_scan[FRONT_T / 64];
+  __shared__ uint32_t s_cls[NBUCKET], s_base[NBUCKET], s_vis;
+  const uint32_t t = threadIdx.x;
+  const ViewP& c = P.view[0];
+  const uint32_t NB = c.nbins, nw = (NB + 1) >> 1;
+  uint32_t* hist = lds;       // 16-bit counters, then ranks
+  uint32_t* base = lds + nw;  // first entry of each tile
+  for (uint32_t i = t; i < nw; i += FRONT_T) hist[i] = 0;
+  if (t < NBUCKET) s_cls[t] = 0;
+  if (t == 0) s_vis = 0;
+  __syncthreads();
+  float px[FRONT_P], py[FRONT_P], pz[FRONT_P], ps[FRONT_P], pa[FRONT_P];
+#pragma unroll
+  for (int q = 0; q < FRONT_P; ++q) {
+    const uint32_t p = min(q * FRONT_T + t, uint32_t(P.n) - 1u);  // (a valid point; n > 0)
+    px[q] = X[p]; py[q] = Y[p]; pz[q] = Z[p]; ps[q] = SW[p]; pa[q] = A[p];
+  }
+  constexpr uint32_t NONE = ~0u;
+  uint32_t br[FRONT_P][NSLOT];  // tile | place in the tile << 16 of each entry
+  uint32_t ez[FRONT_P];
+  float eu[FRONT_P][2], ev[FRONT_P][2], ei[FRONT_P][2];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < FRONT_P; ++q) {
+#pragma unroll
+    for (int k = 0; k < NSLOT; ++k) br[q][k] = NONE;
+    if (q * FRONT_T + t < uint32_t(P.n))
+      for_each_entry<true>(P, c, px[q], py[q], pz[q], ps[q],
+                           [&](uint32_t bin, uint32_t slot, int sel, const Foot& ft, const Geo& g) {
+                             const uint32_t r = bin | add16(hist, bin) << 16;
+#pragma unroll
+                             for (int k = 0; k < NSLOT; ++k) br[q][k] = slot == uint32_t(k) ? r : br[q][k];
+                             ez[q] = __float_as_uint(g.zc);
+                             eu[q][sel] = ft.u;
+                             ev[q][sel] = ft.v;
+                             ei[q][sel] = g.io[sel] * pa[q];
+                           });
+  }
+  __syncthreads();
+  // a run of tiles per thread: its sums, their exclusive scan, then the tables of its tiles
+  const uint32_t per = (NB + FRONT_T - 1) / FRONT_T;
+  const uint32_t b0 = min(NB, t * per), b1 = min(NB, b0 + per);
+  auto count_of = [&](uint32_t b) {
+    return tile_count_of((hist[b >> 1] >> ((b & 1u) * 16u)) & 0xffffu, true, P.item_e, P.fine_e);
+  };
+  uint4 sum = make_uint4(0u, 0u, 0u, 0u);
+  for (uint32_t b = b0; b < b1; ++b) {
+    const TileCount k = count_of(b);
+    sum.x += k.e; sum.y += k.it; sum.z += k.multi; sum.w += k.fine;
+    if (k.it) atomicAdd(&s_cls[item_class(k, P.item_e)], k.it);
+  }
+  uint4 all;
+  uint4 o = block_excl_scan4<FRONT_T / 64>(sum, s_scan, all);
+  if (t == 0) {
+    bin_start[NB] = all.x;
+    item_start[NB] = all.y;
+    info[0] = all.x; info[1] = all.y; info[3] = all.z; info[4] = all.w;
+    uint32_t first = 0;
+    for (int q = 0; q < NBUCKET; ++q) {
+      info[INFO_BUCKET + q] = s_base[q] = first;
+      info[INFO_BUCKET + NBUCKET + q] = 0;
+      first += s_cls[q];
+    }
+  }
+  __syncthreads();
+  for (uint32_t b = b0; b < b1; ++b) {
+    const TileCount k = count_of(b);
+    base[b] = o.x;
+    bin_start[b] = o.x;
+    item_start[b] = o.y;
+    if (k.fine) fine_work[o.w] = make_uint4(b, o.x, o.x + k.e, 0u);
+    if (k.it) {
+      // the partial-list slot of a tile of several items: the items of such tiles before it
+      const uint32_t pslot = k.multi ? o.y - (b - o.z - o.w) : 0u;
+      if (k.multi) { multi_bins[o.z] = b; multi_bins[NB + o.z] = pslot; }
+      const uint32_t at = atomicAdd(&s_base[item_class(k, P.item_e)], k.it);
+      for (uint32_t q = 0; q < k.it; ++q) {
+        const uint32_t e0 = o.x + q * P.item_e;
+        work[at + q] = make_uint4(b, e0, min(e0 + P.item_e, o.x + k.e), k.multi ? (pslot + q) | 0x80000000u : 0u);
+      }
+    }
+    o.x += k.e; o.y += k.it; o.z += k.multi; o.w += k.fine;
+  }
+  for (uint32_t i = t; i <= all.x / 64; i += FRONT_T) kept[i] = 0;
+  __syncthreads();
+  uint32_t vis = 0;
+#pragma unroll
+  for (int q = 0; q < FRONT_P; ++q) {
+    const uint32_t p = q * FRONT_T + t;
+    uint32_t er[NSLOT];
+    bool any = false;
+#pragma unroll
+    for (int k = 0; k < NSLOT; ++k) {
+      er[k] = 0u;
+      if (br[q][k] != NONE) {
+        any = true;
+        er[k] = base[br[q][k] & 0xffffu] + (br[q][k] >> 16);
+        ent[er[k]] = Entry{p, ez[q], eu[q][k / 4], ev[q][k / 4], ei[q][k / 4]};
+      }
+    }
+    if (any) {  // where the backward finds the rows of this point's entries
+      uint4* ep4 = reinterpret_cast<uint4*>(epos + size_t(p) * NSLOT);
+      ep4[0] = make_uint4(er[0], er[1], er[2], er[3]);
+      ep4[1] = make_uint4(er[4], er[5], er[6], er[7]);
+    }
+    vis += any ? 1u : 0u;
+  }
+  atomicAdd(&s_vis, vis);
+  __syncthreads();
+  if (t == 0) info[2] = s_vis;
+}
+
 // Corners of entry e that lie in tile (tx, ty): corner c = 2 dj + di is present iff bit c
 // of the returned mask is set; cs[c] then holds its local texel id and weights.
 struct Corner { int p; float wx, wy; float sx, sy; };
@@ -3344,51 +3475,60 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
   uint32_t* kslot = reinterpret_cast<uint32_t*>(sv + lay.s_kslot);
   uint64_t* kept = reinterpret_cast<uint64_t*>(sv + lay.s_kept);
 
-  if (P.nblk > 0) {
-    StageTimer tm(ST_COUNT, st);
-    hipLaunchKernelGGL(k_count, dim3(P.nblk * P.V), dim3(BIN_THREADS), count_lds(lay.nbv_max), st,
-                       P, pts.x, pts.y, pts.z, pts.size_w, H16);
-  }
-  TRIPS_HIP(hipGetLastError());
-  {
-    StageTimer tm(ST_COLSCAN, st);
-    if (P.nblk > 0) {  // also writes the chunk sums
-      hipLaunchKernelGGL(k_colscan, dim3((P.NB + 63) / 64), dim3(64 * CS_SEG), 0, st, H16, H, tot,
-                         P.NB, P.nblk, csum, P.item_e, P.fine_e);
-    } else {
-      hipLaunchKernelGGL(k_fill_u32, dim3((P.NB + 255) / 256), dim3(256), 0, st, tot, P.NB, 0u);
-      hipLaunchKernelGGL(k_chunksum, dim3(nch), dim3(CHUNK), 0, st, tot, csum, P.NB, P.item_e,
-                         P.fine_e);
-    }
-  }
-  TRIPS_HIP(hipGetLastError());
-  {
-    StageTimer tm(ST_BINSCAN, st);
-    if (nch <= FUSE_CHUNKS) {
-      hipLaunchKernelGGL(k_binscan<true>, dim3(nch), dim3(CHUNK), 0, st, tot, csum, coff,
-                         bin_start, item_start, multi_bins, fine_work, info, work,
-                         P.NB, nch, P.item_e, P.fine_e);
-    } else {
-      hipLaunchKernelGGL(k_chunkscan, dim3(1), dim3(1024), 0, st, csum, coff, bin_start,
-                         item_start, info, P.NB, nch);
-      hipLaunchKernelGGL(k_binscan<false>, dim3(nch), dim3(CHUNK), 0, st, tot, csum, coff,
-                         bin_start, item_start, multi_bins, fine_work, info, work,
-                         P.NB, nch, P.item_e, P.fine_e);
-    }
-  }
-  TRIPS_HIP(hipGetLastError());
-  if (P.nblk > 0) {
+  // few points in a single view are binned by one workgroup, if its tables fit in LDS
+  if (P.n > 0 && P.n <= int64_t(FRONT_N) && P.V == 1 && staged_scatter_lds(lay.nbv_max) <= kLdsLimit) {
     StageTimer tm(ST_SCATTER, st);
-    if (staged_scatter_lds(lay.nbv_max) <= kLdsLimit)
-      hipLaunchKernelGGL(k_scatter<true>, dim3(P.nblk * P.V), dim3(BIN_THREADS),
-                         staged_scatter_lds(lay.nbv_max), st, P, pts.x, pts.y, pts.z, pts.size_w,
-                         pts.opacity, H, bin_start, ent, epos, kept, info);
-    else
-      hipLaunchKernelGGL(k_scatter<false>, dim3(P.nblk * P.V), dim3(BIN_THREADS),
-                         count_lds(lay.nbv_max), st, P, pts.x, pts.y, pts.z, pts.size_w,
-                         pts.opacity, H, bin_start, ent, epos, kept, info);
+    hipLaunchKernelGGL(k_front, dim3(1), dim3(FRONT_T), staged_scatter_lds(lay.nbv_max), st, P,
+                       pts.x, pts.y, pts.z, pts.size_w, pts.opacity, bin_start, item_start,
+                       multi_bins, fine_work, info, work, ent, epos, kept);
+    TRIPS_HIP(hipGetLastError());
+  } else {
+    if (P.nblk > 0) {
+      StageTimer tm(ST_COUNT, st);
+      hipLaunchKernelGGL(k_count, dim3(P.nblk * P.V), dim3(BIN_THREADS), count_lds(lay.nbv_max), st,
+                         P, pts.x, pts.y, pts.z, pts.size_w, H16);
+    }
+    TRIPS_HIP(hipGetLastError());
+    {
+      StageTimer tm(ST_COLSCAN, st);
+      if (P.nblk > 0) {  // also writes the chunk sums
+        hipLaunchKernelGGL(k_colscan, dim3((P.NB + 63) / 64), dim3(64 * CS_SEG), 0, st, H16, H, tot,
+                           P.NB, P.nblk, csum, P.item_e, P.fine_e);
+      } else {
+        hipLaunchKernelGGL(k_fill_u32, dim3((P.NB + 255) / 256), dim3(256), 0, st, tot, P.NB, 0u);
+        hipLaunchKernelGGL(k_chunksum, dim3(nch), dim3(CHUNK), 0, st, tot, csum, P.NB, P.item_e,
+                           P.fine_e);
+      }
+    }
+    TRIPS_HIP(hipGetLastError());
+    {
+      StageTimer tm(ST_BINSCAN, st);
+      if (nch <= FUSE_CHUNKS) {
+        hipLaunchKernelGGL(k_binscan<true>, dim3(nch), dim3(CHUNK), 0, st, tot, csum, coff,
+                           bin_start, item_start, multi_bins, fine_work, info, work,
+                           P.NB, nch, P.item_e, P.fine_e);
+      } else {
+        hipLaunchKernelGGL(k_chunkscan, dim3(1), dim3(1024), 0, st, csum, coff, bin_start,
+                           item_start, info, P.NB, nch);
+        hipLaunchKernelGGL(k_binscan<false>, dim3(nch), dim3(CHUNK), 0, st, tot, csum, coff,
+                           bin_start, item_start, multi_bins, fine_work, info, work,
+                           P.NB, nch, P.item_e, P.fine_e);
+      }
+    }
+    TRIPS_HIP(hipGetLastError());
+    if (P.nblk > 0) {
+      StageTimer tm(ST_SCATTER, st);
+      if (staged_scatter_lds(lay.nbv_max) <= kLdsLimit)
+        hipLaunchKernelGGL(k_scatter<true>, dim3(P.nblk * P.V), dim3(BIN_THREADS),
+                           staged_scatter_lds(lay.nbv_max), st, P, pts.x, pts.y, pts.z, pts.size_w,
+                           pts.opacity, H, bin_start, ent, epos, kept, info);
+      else
+        hipLaunchKernelGGL(k_scatter<false>, dim3(P.nblk * P.V), dim3(BIN_THREADS),
+                           count_lds(lay.nbv_max), st, P, pts.x, pts.y, pts.z, pts.size_w,
+                           pts.opacity, H, bin_start, ent, epos, kept, info);
+    }
+    TRIPS_HIP(hipGetLastError());
   }
-  TRIPS_HIP(hipGetLastError());
   {
     // the fine tiles on the side stream, beside the work items and their merge
     SideStream* sd = nullptr;
@@ -3412,7 +3552,7 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
     }
     hipError_t e1 = hipGetLastError();
     hipError_t e2 = hipEventRecord(sd->join, sd->s);
-    {
+    if (P.n > int64_t(P.item_e)) {  // (a tile has at most one entry per point)
       StageTimer tm(ST_FWD_MERGE, st);
       hipLaunchKernelGGL(k_fwd_merge<D>, dim3(1024), dim3(256), 0, st, P, item_start, multi_bins,
                          info, pcnt, pkey, pgam, pts.desc, pyr, npix, kkey, kgam, X.bg, X.alpha);

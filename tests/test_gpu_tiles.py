@@ -46,3 +46,17 @@ def test_equal_depths_in_the_lists(gpu, D, coarser, item, n):
                              depth_ties=True)
     r = _check(sc, gpu, tp.make_tuning(16, 0, item), coarser)
     assert r.tile_stats()[0].max() > 256
+
+
+@pytest.mark.parametrize("n,tile_w,item", [(1, 16, 0), (1023, 8, 256), (4095, 64, 0),
+                                           (4096, 16, 300), (4097, 16, 300)])
+def test_point_counts_around_the_single_workgroup_binning(gpu, n, tile_w, item):
+    """Up to 4096 points in one view are binned by one workgroup, more by four passes: one point,
+    a count no thread count divides, both sides of the limit, tiles cut into several items."""
+    import paper_2401_06003_amd as tp
+    sc = scenes.random_small(30 + n % 7, n=n, W=150, H=99, nlayers=5, s_lo=0.3, s_hi=30.0)
+    r = _check(sc, gpu, tp.make_tuning(tile_w, 256, item))
+    st = r.stats()
+    assert st["entries"] >= st["visible"]
+    if item:
+        assert st["items"] > st["bins"]  # some tile has several items
