@@ -58,5 +58,5 @@ def test_point_counts_around_the_single_workgroup_binning(gpu, n, tile_w, item):
     r = _check(sc, gpu, tp.make_tuning(tile_w, 256, item))
     st = r.stats()
     assert st["entries"] >= st["visible"]
-    if item:
+    if n >= 4096:
         assert st["items"] > st["bins"]  # some tile has several items
