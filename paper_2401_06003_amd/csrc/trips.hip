@@ -1100,6 +1100,21 @@ constexpr int SUB_F = 4 * SUB_E;      // fragments per LDS round (at most 4 per 
 constexpr uint32_t ENT_BLK = 4;       // consecutive entries taken together by fwd_items
 constexpr uint32_t RND_BLK = SUB_E / ENT_BLK;  // blocks per round
 
+// fwd_select: workgroup size, fragments held in LDS, bins a texel's depths are counted in,
+// longest run whose ranks are counted, entries of a thread in flight
+constexpr int FI_T = 512;
+constexpr uint32_t FI_CAP = 5632;
+constexpr int FI_BINS = 64;
+constexpr uint32_t FI_RUN = 128;
+constexpr uint32_t FI_AHEAD = 2;
+static_assert(FI_CAP >= uint32_t(KEEP) * TP, "the kept lists of a tile fit");
+// Up to SELECT_POINTS (point, view) pairs the work items are too few to fill the chip, and the
+// forward lasts as long as its longest item: fwd_select, whose items are shorter, is the faster
+// one.  Above, it reads the entries three times where fwd_items reads them once.  Forward of
+// 1920x1080, 7 layers, fwd_items against fwd_select: 64k points 170 / 113 us, 500k 189 / 130,
+// 1M 196 / 162, 1.5M 233 / 225 (in Morton order 230 / 236), 2M 275 / 280 (Morton 262 / 310).
+constexpr uint64_t SELECT_POINTS = 1250000;
+
 // Compare-exchange of (key, gamma) pairs: afterwards a holds the smaller key.
 __device__ __forceinline__ void cswap(uint64_t& ka, float& ga, uint64_t& kb, float& gb) {
   const bool sw = kb < ka;
@@ -1314,6 +1329,371 @@ __global__ __launch_bounds__(256) void k_fwd_items(
                              uint32_t(kk[m + 1] >> 32));
 #pragma unroll
     for (int m = 0; m < KEEP; m += 4) pg[m / 4] = make_float4(kg[m], kg[m + 1], kg[m + 2], kg[m + 3]);
+  }
+}
+
+// fwd_select: the work items again, one workgroup each, for clouds of few points (SELECT_POINTS).
+// Of a texel's fragments only the 16 front-most are wanted, so the item's entries are streamed
+// instead of being sorted:
+//  - the first pass counts every fragment in its texel's depth bin (FI_BINS bins over the
+//    depth range of a sample of the item; depths outside fall into the first or last bin).
+//    The bin in which a texel's count reaches 16 bounds its kept fragments from above;
+//  - if the fragments below all bounds do not fit in LDS, or one texel has too many, each
+//    texel's bound bin is divided again over its (depth, index) keys.  A bin of one key is
+//    reached after at most 12 such passes, and then exactly 16 fragments per texel remain;
+//  - the last pass gathers the fragments below the bounds, run after run per texel.
+// Every gathered fragment counts the smaller keys of its run: its rank, and the ranks below 16
+// are the texel's list.  An item of few entries skips the bins: all its fragments fit.  The
+// items of a tile are the same ranges as fwd_items' (in a row, not strided) and the result is
+// the same whatever the order of the entries.
+// Bound by latency and LDS (two workgroups of 512 threads per CU); an item of 8192 entries takes
+// 50 us where 16 rounds of fwd_items take 103; 350k points at 1237x823, D = 8: 110 -> 66 us,
+// 4096 points at 256x256: 36 -> 18 us.
+template <int D>
+__global__ __launch_bounds__(FI_T, 4) void k_fwd_select(
+    const Params P, const uint32_t* __restrict__ info, const uint4* __restrict__ work,
+    const Entry* __restrict__ ent, const float* __restrict__ desc, float* __restrict__ pyr,
+    uint32_t* __restrict__ npix, uint64_t* __restrict__ kkey, float* __restrict__ kgam,
+    uint32_t* __restrict__ pcnt, uint64_t* __restrict__ pkey, float* __restrict__ pgam,
+    const float* __restrict__ bg, float* __restrict__ alpha) {
+  constexpr int NW = FI_T / 64;
+  constexpr int FPT = (int(FI_CAP) + FI_T - 1) / FI_T;  // gathered fragments per thread
+  // one region, used in turn for the depth bins, the gathered fragments and the sorted lists
+  constexpr size_t GATHER_BYTES = size_t(FI_CAP) * 13;
+  constexpr size_t BIN_BYTES = size_t(FI_BINS) * TP * 4;
+  constexpr size_t LIST_BYTES = size_t(KEEP) * TP * 12 + size_t(TP) * (D + 1) * 4;
+  constexpr size_t REGION = GATHER_BYTES > BIN_BYTES ? (GATHER_BYTES > LIST_BYTES ? GATHER_BYTES : LIST_BYTES)
+                                                     : (BIN_BYTES > LIST_BYTES ? BIN_BYTES : LIST_BYTES);
+  __shared__ __align__(16) char region[REGION];
+  __shared__ uint64_t s_lo[TP];    // keys of the bin being divided: [s_lo, s_thr)
+  __shared__ uint64_t s_thr[TP];   // gathered: keys below it
+  __shared__ uint32_t s_pos[TP];   // fragment count, then the next free slot of the run
+  __shared__ uint32_t s_sh[TP];    // bin width of the divided bin (log2), later the run start
+  __shared__ uint32_t s_red[2 * NW];
+  __shared__ uint32_t s_state[2];
+  __shared__ uint32_t s_n[TP];
+  uint32_t* bins = reinterpret_cast<uint32_t*>(region);
+  uint64_t* skey = reinterpret_cast<uint64_t*>(region);
+  float* sgam = reinterpret_cast<float*>(region + size_t(FI_CAP) * 8);
+  uint8_t* stex = reinterpret_cast<uint8_t*>(region + size_t(FI_CAP) * 12);
+  uint64_t* lkey = reinterpret_cast<uint64_t*>(region);                      // [KEEP][TP]
+  float* lgam = reinterpret_cast<float*>(region + size_t(KEEP) * TP * 8);    // [KEEP][TP]
+  float* lcol = reinterpret_cast<float*>(region + size_t(KEEP) * TP * 12);   // [D + 1][TP]
+  const uint32_t total = info[1];
+  const uint32_t slot = blockIdx.x;
+  const uint4 wk = work[slot];  // in bounds (grid = capacity); used only if valid
+  if (slot >= total) return;
+  const int t = threadIdx.x;
+  const uint32_t b = wk.x, it = wk.w & 0x7fffffffu;
+  const bool multi = (wk.w >> 31) != 0;
+  const BinInfo bi = decode_bin(P, b);
+  const uint32_t e0 = wk.y, e1 = wk.z;
+  const TileGeo tg = tile_geo(bi, P.ltw);
+  const int tw = 1 << P.ltw;
+  // Calls f(entry) for every entry of the item: FI_AHEAD entries of a thread are loaded together,
+  // while the FI_AHEAD before them are worked on.  The lanes of a wavefront take blocks of 4
+  // consecutive entries from 16 places of the step's entries: neighbours in a spatially ordered
+  // cloud fall on the same texel, and their LDS atomics would wait for one another.
+  constexpr uint32_t STEP = FI_AHEAD * FI_T;
+  const uint32_t apart = min(STEP, (e1 - e0 + 63u) & ~63u) / 16u;  // places of a step
+  auto stream = [&](auto&& f) {
+    uint32_t at[FI_AHEAD];  // a thread's entries of a step (FREE: none)
+    constexpr uint32_t FREE = 1u << 30;
+#pragma unroll
+    for (uint32_t q = 0; q < FI_AHEAD; ++q) {
+      const uint32_t u = q * FI_T + t, in = (u >> 6) * 4u;
+      at[q] = in < apart ? (u & 3u) + ((u >> 2) & 15u) * apart + in : FREE;
+    }
+    const uint32_t ne = e1 - e0;
+    Entry e[FI_AHEAD];
+#pragma unroll
+    for (uint32_t q = 0; q < FI_AHEAD; ++q)
+      if (at[q] < ne) e[q] = ent[e0 + at[q]];
+    for (uint32_t p = 0; p < ne; p += STEP) {
+      Entry n[FI_AHEAD];
+#pragma unroll
+      for (uint32_t q = 0; q < FI_AHEAD; ++q)
+        if (at[q] + p + STEP < ne) n[q] = ent[e0 + at[q] + p + STEP];
+#pragma unroll
+      for (uint32_t q = 0; q < FI_AHEAD; ++q)
+        if (at[q] + p < ne) f(e[q]);
+#pragma unroll
+      for (uint32_t q = 0; q < FI_AHEAD; ++q) e[q] = n[q];
+    }
+  };
+  uint32_t n = 0;      // fragments of texel t (threads below TP)
+  uint32_t sel = 0;    // of them gathered
+  // do the gathered fragments fit?  (runs are padded to whole steps of the rank count)
+  auto fits = [&]() {
+    if (t == 0) { s_state[0] = 0; s_state[1] = 0; }
+    __syncthreads();
+    if (t < TP) {
+      const uint32_t w = wave_sum_u32((sel + 3u) & ~3u);
+      if ((t & 63) == 0) atomicAdd(&s_state[0], w);
+      if (sel > FI_RUN) s_state[1] = 1;
+    }
+    __syncthreads();
+    return s_state[0] <= FI_CAP && s_state[1] == 0;
+  };
+  bool direct = (e1 - e0) * 4 <= FI_CAP;
+  if (direct) {
+    if (t < TP) { s_pos[t] = 0; s_thr[t] = KEY_NONE; }
+    __syncthreads();
+    stream([&](const Entry& e) {
+      float fu, fv;
+      const int pm = tile_corners(tg, e.u, e.v, fu, fv), p = pm >> 4;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if ((pm >> c) & 1) atomicAdd(&s_pos[p + (c & 1) + (c >> 1) * tw], 1u);
+    });
+    __syncthreads();
+    if (t < TP) n = sel = s_pos[t];
+    direct = fits();
+  }
+  if (!direct) {
+    // depth range of a sample: the item's first FI_T entries
+    uint32_t z0, z1;
+    {
+      const uint32_t z = ent[min(e0 + t, e1 - 1)].zbits;
+      z0 = z1 = z;
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) {
+        z0 = min(z0, uint32_t(__shfl_xor(z0, m, 64)));
+        z1 = max(z1, uint32_t(__shfl_xor(z1, m, 64)));
+      }
+      if ((t & 63) == 0) { s_red[t >> 6] = z0; s_red[NW + (t >> 6)] = z1; }
+    }
+    for (int k = t; k < FI_BINS * TP / 4; k += FI_T)
+      reinterpret_cast<uint4*>(bins)[k] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NW; ++k) { z0 = min(z0, s_red[k]); z1 = max(z1, s_red[NW + k]); }
+    // bin = (depth - z0) * mul / 2^32: below FI_BINS up to z1, monotone in the depth bits
+    const uint32_t mul = uint32_t((uint64_t(FI_BINS) << 32) / (uint64_t(z1 - z0) + FI_BINS + 1));
+    stream([&](const Entry& e) {
+      float fu, fv;
+      const int pm = tile_corners(tg, e.u, e.v, fu, fv), p = pm >> 4;
+      const uint32_t k = min(uint32_t(FI_BINS - 1), __umulhi(max(e.zbits, z0) - z0, mul));
+      const int a = int(k * TP) + p;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if ((pm >> c) & 1) atomicAdd(&bins[a + (c & 1) + (c >> 1) * tw], 1u);
+    });
+    __syncthreads();
+    n = 0;
+    uint32_t base = 0;  // fragments of the texel known to be below the divided bin
+    uint64_t lo = 0, hi = KEY_NONE;
+    if (t < TP) {
+      uint32_t kb = FI_BINS, below = 0;
+#pragma unroll 16
+      for (int k = 0; k < FI_BINS; ++k) {
+        const uint32_t c = bins[k * TP + t];
+        if (kb == FI_BINS && n + c >= KEEP) { kb = k; below = n; sel = n + c; }
+        n += c;
+      }
+      if (kb == FI_BINS) {
+        sel = n;  // fewer than 16: all of them, nothing to divide
+        lo = hi;
+      } else {
+        base = below;
+        // first depth of bin k: the smallest d with d * mul >= k 2^32
+        if (kb > 0) lo = (uint64_t(z0) + ((uint64_t(kb) << 32) + mul - 1) / mul) << 32;
+        if (kb < FI_BINS - 1) hi = (uint64_t(z0) + ((uint64_t(kb + 1) << 32) + mul - 1) / mul) << 32;
+      }
+    }
+    for (;;) {
+      if (t < TP) s_thr[t] = hi;
+      if (fits()) break;
+      // divide every texel's bin [lo, hi) into FI_BINS by its keys
+      uint32_t sh = 0;
+      if (t < TP) {
+        const uint64_t w = hi - lo;  // > 0 unless the texel has no bin to divide
+        sh = w > FI_BINS ? uint32_t(64 - __clzll((long long)((w - 1) / FI_BINS))) : 0u;
+        s_lo[t] = lo;
+        s_sh[t] = sh;
+      }
+      for (int k = t; k < FI_BINS * TP / 4; k += FI_T)
+        reinterpret_cast<uint4*>(bins)[k] = make_uint4(0u, 0u, 0u, 0u);
+      __syncthreads();
+      stream([&](const Entry& e) {
+        float fu, fv;
+        const int pm = tile_corners(tg, e.u, e.v, fu, fv), p = pm >> 4;
+        const uint64_t key = (uint64_t(e.zbits) << 32) | e.idx;
+        uint64_t l[4], h[4];
+        uint32_t q[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {  // (a corner outside the tile reads some texel of it)
+          q[c] = uint32_t(p + (c & 1) + (c >> 1) * tw) & (TP - 1);
+          l[c] = s_lo[q[c]];
+          h[c] = s_thr[q[c]];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (((pm >> c) & 1) && key >= l[c] && key < h[c])
+            atomicAdd(&bins[uint32_t((key - l[c]) >> s_sh[q[c]]) * TP + q[c]], 1u);
+      });
+      __syncthreads();
+      if (t < TP && lo < hi) {
+        uint32_t m = base, kb = FI_BINS;
+#pragma unroll 16
+        for (int k = 0; k < FI_BINS; ++k) {
+          const uint32_t c = bins[k * TP + t];
+          if (kb == FI_BINS && m + c >= KEEP) { kb = k; base = m; sel = m + c; }
+          m += c;
+        }
+        if (kb < FI_BINS) {  // (always: the bin held the 16th fragment)
+          const uint64_t h = lo + ((uint64_t(kb) + 1) << sh);
+          hi = h > lo && h < hi ? h : hi;
+          lo += uint64_t(kb) << sh;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  // runs of the gathered fragments, one per texel, padded to multiples of four with KEY_NONE
+  uint32_t tot, start;
+  {
+    const uint32_t x = t < TP ? (sel + 3u) & ~3u : 0u;
+    start = block_excl_scan<NW>(x, s_red, tot);
+    if (t < TP) {
+      s_sh[t] = start;
+      s_pos[t] = start;
+      for (uint32_t q = sel; q < x; ++q)
+        if (start + q < FI_CAP) skey[start + q] = KEY_NONE;
+    }
+    __syncthreads();
+  }
+  stream([&](const Entry& e) {
+    float fu, fv;
+    const int pm = tile_corners(tg, e.u, e.v, fu, fv), p = pm >> 4;
+    const uint64_t key = (uint64_t(e.zbits) << 32) | e.idx;
+    uint64_t h[4];
+    uint32_t q[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      q[c] = uint32_t(p + (c & 1) + (c >> 1) * tw) & (TP - 1);
+      h[c] = s_thr[q[c]];
+    }
+    uint32_t o[4];  // (all four slots are drawn before any is written)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      o[c] = FI_CAP;
+      if (((pm >> c) & 1) && key < h[c]) o[c] = atomicAdd(&s_pos[q[c]], 1u);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (o[c] < FI_CAP) {
+        skey[o[c]] = key;
+        sgam[o[c]] = (((c & 1) ? fu : 1.0f - fu) * ((c >> 1) ? fv : 1.0f - fv)) * e.ia;
+        stex[o[c]] = uint8_t(q[c]);
+      }
+  });
+  __syncthreads();
+  // rank of every gathered fragment in its run: the smaller keys of the run
+  uint64_t fk[FPT];
+  float fg[FPT];
+  uint32_t fo[FPT];  // list slot [rank][texel]
+#pragma unroll
+  for (int q = 0; q < FPT; ++q) {
+    const uint32_t o = t + q * FI_T;
+    fo[q] = KEEP * TP;
+    fk[q] = o < tot ? skey[o] : KEY_NONE;
+    if (fk[q] != KEY_NONE) {
+      fg[q] = sgam[o];
+      const uint32_t p = stex[o], r1 = s_pos[p];
+      uint32_t rk = 0;
+      for (uint32_t r = s_sh[p]; r < r1; r += 4) {
+        const ulonglong2 ka = *reinterpret_cast<const ulonglong2*>(&skey[r]);
+        const ulonglong2 kb = *reinterpret_cast<const ulonglong2*>(&skey[r + 2]);
+        rk += (ka.x < fk[q] ? 1u : 0u) + (ka.y < fk[q] ? 1u : 0u);
+        rk += (kb.x < fk[q] ? 1u : 0u) + (kb.y < fk[q] ? 1u : 0u);
+      }
+      fo[q] = rk * TP + p;
+    }
+  }
+  if (t < TP) s_n[t] = n;
+  __syncthreads();  // the gathered fragments are in registers: the region takes the lists
+#pragma unroll
+  for (int q = 0; q < FPT; ++q)
+    if (fo[q] < KEEP * TP) { lkey[fo[q]] = fk[q]; lgam[fo[q]] = fg[q]; }
+  __syncthreads();
+  // FI_T / TP threads per texel, each with LQ consecutive slots of its list
+  constexpr int LQ = KEEP * TP / FI_T;
+  const int x = t & (TP - 1), m0 = (t / TP) * LQ;
+  const uint32_t nx = s_n[x], k = min(nx, uint32_t(KEEP));
+  uint64_t kk[LQ];
+  float kg[LQ];
+#pragma unroll
+  for (int q = 0; q < LQ; ++q) {
+    const bool v = uint32_t(m0 + q) < k;
+    kk[q] = v ? lkey[(m0 + q) * TP + x] : KEY_NONE;
+    kg[q] = v ? lgam[(m0 + q) * TP + x] : 0.0f;
+  }
+  if (multi) {
+    // partial list of this texel: 16 keys and gammas stored contiguously (unused slots hold
+    // KEY_NONE), read back as whole lists by the merge
+    if (t < TP) pcnt[size_t(it) * TP + x] = nx;
+    uint4* pk = reinterpret_cast<uint4*>(pkey + (size_t(it) * TP + x) * KEEP + m0);
+    float4* pg = reinterpret_cast<float4*>(pgam + (size_t(it) * TP + x) * KEEP + m0);
+#pragma unroll
+    for (int q = 0; q < LQ; q += 2)
+      pk[q / 2] = make_uint4(uint32_t(kk[q]), uint32_t(kk[q] >> 32), uint32_t(kk[q + 1]),
+                             uint32_t(kk[q + 1] >> 32));
+#pragma unroll
+    for (int q = 0; q < LQ; q += 4) pg[q / 4] = make_float4(kg[q], kg[q + 1], kg[q + 2], kg[q + 3]);
+    return;
+  }
+  float4 tv[LQ][D / 4];
+#pragma unroll
+  for (int q = 0; q < LQ; ++q) {
+    const float4* tp = reinterpret_cast<const float4*>(desc + size_t(uint32_t(kk[q])) * D);
+#pragma unroll
+    for (int r = 0; r < D / 4; ++r)
+      tv[q][r] = uint32_t(m0 + q) < k ? tp[r] : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+#pragma unroll
+  for (int q = 0; q < LQ; ++q)
+    if (uint32_t(m0 + q) < k) {
+      kkey[(size_t(b) * KEEP + m0 + q) * TP + x] = kk[q];
+      kgam[(size_t(b) * KEEP + m0 + q) * TP + x] = kg[q];
+    }
+  // blend front to back: a texel's threads take colour and transmittance from the one before
+  // them in LDS
+  float C[D], T = 1.0f;
+#pragma unroll
+  for (int d = 0; d < D; ++d) C[d] = 0.0f;
+#pragma unroll 1
+  for (int h = 0; h < FI_T / TP; ++h) {
+    if (t / TP == h) {
+      if (h > 0) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) C[d] = lcol[d * TP + x];
+        T = lcol[D * TP + x];
+      }
+#pragma unroll
+      for (int q = 0; q < LQ; ++q)
+        if (uint32_t(m0 + q) < k) {
+          const float w = T * kg[q];
+#pragma unroll
+          for (int r = 0; r < D / 4; ++r) {
+            C[4 * r + 0] += w * tv[q][r].x;
+            C[4 * r + 1] += w * tv[q][r].y;
+            C[4 * r + 2] += w * tv[q][r].z;
+            C[4 * r + 3] += w * tv[q][r].w;
+          }
+          T = T * (1.0f - kg[q]);
+        }
+#pragma unroll
+      for (int d = 0; d < D; ++d) lcol[d * TP + x] = C[d];
+      lcol[D * TP + x] = T;
+    }
+    __syncthreads();
+  }
+  if (t >= FI_T - TP) {
+    const int i = tg.x0 + (x & (tw - 1)), j = tg.y0 + (x >> P.ltw);
+    if (i < bi.WL && j < bi.HL)
+      write_texel<D>(C, T, size_t(P.view[bi.v].lout[bi.L]) + size_t(j) * bi.WL + i, pyr, bg, alpha);
+    npix[size_t(b) * TP + x] = nx;
   }
 }
 
@@ -3539,9 +3919,14 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
     {  // one workgroup per work item (the longer path, enqueued first); workgroups beyond the
        // item count exit at once
       StageTimer tm(ST_FWD_ITEMS, st);
-      hipLaunchKernelGGL(k_fwd_items<D>, dim3(uint32_t(lay.icap)), dim3(256), 0, st, P, info,
-                         work, bin_start, item_start, ent, pts.desc, pyr, npix, kkey, kgam, pcnt,
-                         pkey, pgam, X.bg, X.alpha);
+      if (uint64_t(P.n) * uint64_t(P.V) <= SELECT_POINTS && !P.coarser)
+        hipLaunchKernelGGL(k_fwd_select<D>, dim3(uint32_t(lay.icap)), dim3(FI_T), 0, st, P, info,
+                           work, ent, pts.desc, pyr, npix, kkey, kgam, pcnt, pkey, pgam, X.bg,
+                           X.alpha);
+      else
+        hipLaunchKernelGGL(k_fwd_items<D>, dim3(uint32_t(lay.icap)), dim3(256), 0, st, P, info,
+                           work, bin_start, item_start, ent, pts.desc, pyr, npix, kkey, kgam, pcnt,
+                           pkey, pgam, X.bg, X.alpha);
     }
     hipError_t e3 = hipGetLastError();
     hipError_t e0 = hipStreamWaitEvent(sd->s, sd->fork, 0);

@@ -60,3 +60,18 @@ def test_point_counts_around_the_single_workgroup_binning(gpu, n, tile_w, item):
     assert st["entries"] >= st["visible"]
     if n >= 4096:
         assert st["items"] > st["bins"]  # some tile has several items
+
+
+@pytest.mark.parametrize("n,W,H,nl,item,ties", [
+    (1500, 16, 16, 1, 0, False),     # one tile, more fragments than fit, hundreds per texel
+    (1500, 16, 16, 1, 0, True),      # ... of four depths: bins divided down to single keys
+    (20000, 24, 20, 2, 0, True),     # items of 8192 entries, thousands of equal depths per texel
+    (20000, 70, 50, 3, 777, False),  # tiles of many items, partial lists merged
+    (1300, 33, 17, 3, 0, False)])    # around the item size whose fragments all fit
+def test_lists_selected_by_counting(gpu, n, W, H, nl, item, ties):
+    """Items of a few hundred to thousands of entries, whose kept lists are selected by depth bins
+    where their fragments do not fit in LDS."""
+    import paper_2401_06003_amd as tp
+    sc = scenes.random_small(40, n=n, W=W, H=H, nlayers=nl, s_lo=0.4, s_hi=10.0, depth_ties=ties)
+    r = _check(sc, gpu, tp.make_tuning(16, 0, item))
+    assert r.tile_stats()[0].max() > 300
