@@ -2029,18 +2029,20 @@ __device__ __forceinline__ float2 blend_adjoint_step(float Tm, float gam, float 
 // Two threads per texel share its list and hand T and B on through LDS, where the results stay.
 // Then each entry finds its corners in the tile's kept lists and writes its partial-gradient row: (A, Bx, By, 0, tau[D]) with A = sum dgamma wx wy,
 // Bx = sum dgamma sx wy, By = sum dgamma wx sy, tau = sum T_m gamma_m G over its corners.
-// The lists are in depth order, so a corner's slot is found by bisection of the texel's 16
-// depths in LDS (five reads instead of a comparison with all 16 point ids).  A fragment as deep
-// as the last kept one is told apart by its point index, and where a list holds equal depths
-// the stored keys are consulted.  An entry without a kept corner writes no row, only its bit in `kept`.
+// A corner is kept iff its key is not above the texel's last kept key; a wavefront collects the
+// entries that have such a corner until every lane holds one.  The lists are in depth order, so a
+// kept corner's slot is found by bisection of the texel's depths in LDS (four reads instead of a
+// comparison with all 16 point ids); where a list holds equal depths the stored keys tell.  An
+// entry without a kept corner writes no row, only its bit in `kept`.
 // With coarser-layer inclusion (INC) the kept own fragments are those the blended list took
 // (a prefix of the own list), and each one's totals (dL/dgamma, tau part) are read from
 // itot instead of being formed from the blend adjoint and G.
 // Bound by the latency of its gathers and the wavefronts in flight (57 KB of LDS: two workgroups
 // of 512 threads per CU).  The adjoint used to be a kernel of its own that passed (dL/dgamma,
 // T gamma) through memory; at 1920x1080, D = 4, the two took 49 + 89 us at 2M points and 141 +
-// 252 us at 8M; bisecting the depths and leaving rows out made the second 77 and 210 us, and one
-// kernel of both takes 115 and 295 us.
+// 252 us at 8M; bisecting the depths and leaving rows out made the second 77 and 210 us, one
+// kernel of both took 115 and 295 us, and collecting the entries that write a row 104 and 264 us
+// (with inclusion, where few entries do, 131 -> 58 us at 2M points).
 template <int D, bool INC, int T>
 __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
     const Params P, const uint32_t* __restrict__ info, const uint4* __restrict__ work,
@@ -2052,7 +2054,7 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
     const float* __restrict__ itot, const Extras X) {
   constexpr int RW = 4 + D;
   constexpr int S = D + 1;
-  constexpr int EB = INC ? 3 : 2;  // entries per thread in flight
+  constexpr int EB = 2;  // entries per thread in flight
   constexpr int H = T / TP, LQ = KEEP / H;  // threads per texel, list slots of each
   static_assert(H <= 2, "T and B are handed on once");
   constexpr uint32_t TIE = 0x80000000u;  // (depth bits of kept fragments are below it)
@@ -2184,97 +2186,114 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
         last = uint32_t(m) < k ? z : last;
       }
       if (k > 0) id = uint32_t(kkey[(size_t(b) * KEEP + (k - 1)) * TP + x]);
-      s_last[x] = make_uint2(last | (tie ? TIE : 0u), id);
+      s_last[x] = make_uint2(k > 0 ? last | (tie ? TIE : 0u) : 0u, id);  // (depths are positive)
     }
   }
   __syncthreads();
-  for (uint32_t e = e0 + t; e - (t & 63) < e1; e += EB * T) {  // (whole wavefronts)
+  // the row of an entry with kept corners (bit mask pm & 15, local texel of corner 0 pm >> 4)
+  auto write_row = [&](uint32_t e, int pm, float u, float v, uint32_t z, uint32_t idx) {
+    const float fu = u - floorf(u), fv = v - floorf(v);
+    uint32_t pos[4];
+    float2 st[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      // (a corner that is not kept bisects some texel of the tile and is dropped)
+      const uint32_t p = uint32_t((pm >> 4) + (q & 1) + ((q >> 1) << P.ltw)) & (TP - 1);
+      uint32_t m = 0;
+#pragma unroll
+      for (uint32_t st2 = KEEP / 2; st2 >= 1; st2 /= 2) m += s_z[m + st2 - 1][p] < z ? st2 : 0u;
+      if (((pm >> q) & 1) && (s_last[p].x & TIE))  // equal depths in the list: the slot with
+        while (m < KEEP - 1 && uint32_t(kkey[(size_t(b) * KEEP + m) * TP + p]) != idx) ++m;
+      pos[q] = m * TP + p;
+    }
+    float itau[4][INC ? D : 1];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool on = (pm >> q) & 1;
+      if (INC) {
+        const float* it = itot + size_t(b) * KEEP * S * TP + size_t(pos[q] / TP) * S * TP + pos[q] % TP;
+        st[q] = make_float2(on ? it[0] : 0.0f, 0.0f);
+#pragma unroll
+        for (int d = 0; d < D; ++d) itau[q][INC ? d : 0] = on ? it[size_t(1 + d) * TP] : 0.0f;
+      } else {
+        st[q] = on ? s_bst[INC ? 0 : pos[q] / TP][INC ? 0 : pos[q] % TP] : make_float2(0.f, 0.f);
+      }
+    }
+    float A = 0.0f, Bx = 0.0f, By = 0.0f;
+    float tau[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) tau[d] = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (!((pm >> q) & 1)) continue;
+      const float wx = (q & 1) ? fu : 1.0f - fu, wy = (q >> 1) ? fv : 1.0f - fv;
+      const float sx = (q & 1) ? 1.0f : -1.0f, sy = (q >> 1) ? 1.0f : -1.0f;
+      const float dg = st[q].x;
+      A += dg * (wx * wy);
+      Bx += dg * (sx * wy);
+      By += dg * (wx * sy);
+#pragma unroll
+      for (int d = 0; d < D; ++d) tau[d] += INC ? itau[q][INC ? d : 0] : st[q].y * s_G[INC ? 0 : pos[q] % TP][d];
+    }
+    float4* r4 = reinterpret_cast<float4*>(rows + size_t(e) * RW);  // rows in entry order
+    r4[0] = make_float4(A, Bx, By, 0.0f);
+#pragma unroll
+    for (int q = 0; q < D / 4; ++q)
+      r4[1 + q] = make_float4(tau[4 * q], tau[4 * q + 1], tau[4 * q + 2], tau[4 * q + 3]);
+  };
+  // A wavefront collects its entries with kept corners (lanes below `waiting` hold one) until it
+  // has one for every lane: about a quarter of the entries keep a fragment, and their rows take
+  // most of the work.
+  const uint32_t lane = t & 63;
+  uint32_t waiting = 0;
+  uint32_t we = 0, wz = 0, wid = 0;
+  int wpm = 0;
+  float wu = 0.0f, wv = 0.0f;
+  for (uint32_t e = e0 + t; e - lane < e1; e += EB * T) {  // (whole wavefronts)
     Entry en[EB];
 #pragma unroll
     for (int q = 0; q < EB; ++q) {
       en[q] = nx[q];
       if (e + (EB + q) * T < e1) nx[q] = ent[e + (EB + q) * T];  // next round of entries
     }
-    // find the kept slot of every corner, then the adjoints of all of them
-    int p0[EB];
-    float fu[EB], fv[EB];
-    uint32_t cm[EB];
-    typename std::conditional<INC, size_t, uint32_t>::type pos[EB][4];
-#pragma unroll
-    for (int h = 0; h < EB; ++h) {
-      const int pm = e + h * T < e1 ? tile_corners(tg, en[h].u, en[h].v, fu[h], fv[h]) : 0;
-      p0[h] = pm >> 4;
-      cm[h] = uint32_t(pm) & 15u;
-      const uint32_t z = en[h].zbits;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        // (a corner outside the tile bisects some texel of it and is dropped)
-        const uint32_t p = uint32_t(p0[h] + (q & 1) + ((q >> 1) << P.ltw)) & (TP - 1);
-        uint32_t m = 0;
-#pragma unroll
-        for (uint32_t st = KEEP / 2; st >= 1; st /= 2) m += s_z[m + st - 1][p] < z ? st : 0u;
-        bool on = ((cm[h] >> q) & 1u) && s_z[m][p] == z;
-        const uint2 last = s_last[p];
-        on = on && (z != last.x || en[h].idx == last.y);
-        if (on && (last.x & TIE)) {
-          // equal depths in the list: the slot with this point's key, if it is kept (the slots
-          // of equal depth are consecutive from m on)
-          on = false;
-          for (; !on && m < KEEP && s_z[m][p] == z; m += on ? 0u : 1u)
-            on = uint32_t(kkey[(size_t(b) * KEEP + m) * TP + p]) == en[h].idx;
-        }
-        cm[h] &= on ? ~0u : ~(1u << q);
-        pos[h][q] = !on ? 0
-                    : INC ? (size_t(b) * KEEP + m) * S * TP + p : m * TP + p;
-      }
-    }
-    float2 st[EB][4];
-    float itau[INC ? EB : 1][4][INC ? D : 1];
-#pragma unroll
-    for (int h = 0; h < EB; ++h)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const bool on = (cm[h] >> q) & 1u;
-        if (INC) {
-          st[h][q] = make_float2(on ? itot[pos[h][q]] : 0.0f, 0.0f);
-#pragma unroll
-          for (int d = 0; d < D; ++d)
-            itau[INC ? h : 0][q][INC ? d : 0] = on ? itot[pos[h][q] + size_t(1 + d) * TP] : 0.0f;
-        } else {
-          st[h][q] = on ? s_bst[INC ? 0 : pos[h][q] / TP][INC ? 0 : pos[h][q] % TP] : make_float2(0.f, 0.f);
-        }
-      }
 #pragma unroll
     for (int h = 0; h < EB; ++h) {
       const uint32_t eh = e + h * T;
-      const uint64_t bits = __ballot(cm[h] != 0);
-      if ((t & 63) == 0) mark_kept(kept, eh, bits);
-      if (cm[h] == 0) continue;
-      float A = 0.0f, Bx = 0.0f, By = 0.0f;
-      float tau[D];
-#pragma unroll
-      for (int d = 0; d < D; ++d) tau[d] = 0.0f;
+      float fu, fv;
+      const int pa = eh < e1 ? tile_corners(tg, en[h].u, en[h].v, fu, fv) : 0;
+      // kept: not behind the texel's last kept fragment
+      int pm = pa & ~15;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        if (!((cm[h] >> q) & 1u)) continue;
-        const int p = p0[h] + (q & 1) + ((q >> 1) << P.ltw);
-        const float wx = (q & 1) ? fu[h] : 1.0f - fu[h], wy = (q >> 1) ? fv[h] : 1.0f - fv[h];
-        const float sx = (q & 1) ? 1.0f : -1.0f, sy = (q >> 1) ? 1.0f : -1.0f;
-        const float dg = st[h][q].x;
-        A += dg * (wx * wy);
-        Bx += dg * (sx * wy);
-        By += dg * (wx * sy);
-#pragma unroll
-        for (int d = 0; d < D; ++d) tau[d] += INC ? itau[INC ? h : 0][q][INC ? d : 0] : st[h][q].y * s_G[INC ? 0 : p][d];
+        const uint2 last = s_last[uint32_t((pa >> 4) + (q & 1) + ((q >> 1) << P.ltw)) & (TP - 1)];
+        const uint32_t lz = last.x & ~TIE;
+        const bool on = ((pa >> q) & 1) && (en[h].zbits < lz || (en[h].zbits == lz && en[h].idx <= last.y));
+        pm |= int(on) << q;
       }
-      float* r = rows + size_t(eh) * RW;  // rows in entry order
-      float4* r4 = reinterpret_cast<float4*>(r);
-      r4[0] = make_float4(A, Bx, By, 0.0f);
-#pragma unroll
-      for (int q = 0; q < D / 4; ++q)
-        r4[1 + q] = make_float4(tau[4 * q], tau[4 * q + 1], tau[4 * q + 2], tau[4 * q + 3]);
+      const bool any = (pm & 15) != 0;
+      const uint64_t bits = __ballot(any);
+      if (bits == 0) continue;  // (uniform)
+      if (lane == 0) mark_kept(kept, eh, bits);
+      // the entries with kept corners move to the lanes from `waiting` on, the others behind them
+      const uint32_t nk = uint32_t(__popcll(bits));
+      const uint32_t before = __builtin_amdgcn_mbcnt_hi(uint32_t(bits >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bits), 0u));
+      const int to = int((waiting + (any ? before : nk + lane - before)) & 63u) * 4;
+      const uint32_t ne = __builtin_amdgcn_ds_permute(to, int(eh)), nz = __builtin_amdgcn_ds_permute(to, int(en[h].zbits));
+      const uint32_t nid = __builtin_amdgcn_ds_permute(to, int(en[h].idx));
+      const int npm = __builtin_amdgcn_ds_permute(to, pm);
+      const float nu = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(en[h].u)));
+      const float nv = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(en[h].v)));
+      if (lane >= waiting) { we = ne; wz = nz; wid = nid; wpm = npm; wu = nu; wv = nv; }
+      if (waiting + nk < 64) {
+        waiting += nk;
+      } else {
+        write_row(we, wpm, wu, wv, wz, wid);
+        we = ne; wz = nz; wid = nid; wpm = npm; wu = nu; wv = nv;
+        waiting += nk - 64;
+      }
     }
   }
+  if (lane < waiting) write_row(we, wpm, wu, wv, wz, wid);
   if (INC) return;
   __syncthreads();  // the next item may overwrite the lists
   }
