@@ -205,7 +205,7 @@ trips_status trips_export_fragments(const trips_config* cfg_host, const trips_ca
 /* Statistics of the forward call that filled `saved`, copied to host memory after a
    stream synchronisation: stats_host[0] = tile entries, [1] = work items (tile pieces of
    at most item_entries entries, and tiles of at most 256 entries, which are rendered whole;
-   with include_coarser only empty tiles are rendered whole),
+   with include_coarser only empty tiles are counted as such),
    [2] = tiles (bins), [3] = (point, view) pairs that wrote at least one fragment.
    For tests and reports; not needed for rendering. */
 trips_status trips_forward_stats(const trips_config* cfg_host, const trips_camera* cams_host,

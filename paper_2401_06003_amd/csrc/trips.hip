@@ -47,9 +47,10 @@ constexpr int MAXL = TRIPS_MAX_LAYERS;
 constexpr uint64_t KEY_NONE = ~0ull;
 // A tile with at most FINE_E entries ("fine" tile, typical of the finest layers) is rendered
 // by one workgroup with one entry per thread: its lists are sorted in LDS, and the kept slot
-// of every corner is stored in the entry for the backward pass.  With coarser-layer
-// inclusion only empty tiles take that path (the backward of every other tile then reads
-// per-slot adjoints that the inclusion pass accumulates).
+// of every corner is stored for the backward pass.  With coarser-layer inclusion the forward
+// renders these tiles the same way, but all except empty ones are work items as well (the
+// backward then takes every tile's rows from per-slot adjoints that the inclusion pass
+// accumulates).
 constexpr uint32_t FINE_E = 256;
 // The backward needs no merge, so its workgroups take smaller parts of the work items.
 constexpr uint32_t BWD_SPLIT = 2;    // with coarser-layer inclusion
@@ -1181,6 +1182,7 @@ __global__ __launch_bounds__(256) void k_fwd_items(
   if (blockIdx.x >= total) return;
   const uint32_t b = wk.x, it = wk.w & 0x7fffffffu;
   const bool multi = (wk.w >> 31) != 0;
+  if (P.coarser && !multi && wk.z - wk.y <= FINE_E) return;  // fwd_fine renders it
   const BinInfo bi = decode_bin(P, b);
   // the item's blocks (uniform): the tile's entries t0..t1, item ii of ni
   uint32_t t0 = wk.y, t1 = wk.z, ni = 1, ii = 0;
@@ -1386,6 +1388,7 @@ __global__ __launch_bounds__(FI_T, 4) void k_fwd_select(
   const int t = threadIdx.x;
   const uint32_t b = wk.x, it = wk.w & 0x7fffffffu;
   const bool multi = (wk.w >> 31) != 0;
+  if (P.coarser && !multi && wk.z - wk.y <= FINE_E) return;  // fwd_fine renders it
   const BinInfo bi = decode_bin(P, b);
   const uint32_t e0 = wk.y, e1 = wk.z;
   const TileGeo tg = tile_geo(bi, P.ltw);
@@ -1712,8 +1715,8 @@ constexpr uint32_t KSLOT_NONE = 31;
 template <int D>
 __global__ __launch_bounds__(256) void k_fwd_fine(
     const Params P, const uint32_t* __restrict__ info, const uint4* __restrict__ fine_work,
-    const Entry* __restrict__ ent, uint32_t* __restrict__ kslot, const float* __restrict__ desc,
-    float* __restrict__ pyr, uint32_t* __restrict__ npix, uint64_t* __restrict__ kkey,
+    const uint32_t* __restrict__ bin_start, const Entry* __restrict__ ent,
+    uint32_t* __restrict__ kslot, const float* __restrict__ desc, float* __restrict__ pyr, uint32_t* __restrict__ npix, uint64_t* __restrict__ kkey,
     float* __restrict__ kgam, const float* __restrict__ bg, float* __restrict__ alpha) {
   constexpr int NF = 4 * FINE_E;     // fragment capacity
   __shared__ uint32_t hist[TP];      // fragments per texel, then the start of its run
@@ -1727,8 +1730,14 @@ __global__ __launch_bounds__(256) void k_fwd_fine(
   __shared__ float4 sdesc[FINE_E][D / 4];  // descriptor of each entry's point
   static_assert(FINE_E == TP, "one entry per thread");
   const int t = threadIdx.x;
-  const uint4 wk = fine_work[blockIdx.x];  // in bounds (grid = bin count); used only if valid
-  if (blockIdx.x >= info[4]) return;
+  uint4 wk;
+  if (P.coarser) {  // (the list holds the empty tiles only; the tiles themselves are looked at)
+    wk = make_uint4(blockIdx.x, bin_start[blockIdx.x], bin_start[blockIdx.x + 1], 0u);
+    if (wk.z - wk.y > FINE_E) return;
+  } else {
+    wk = fine_work[blockIdx.x];  // in bounds (grid = bin count); used only if valid
+    if (blockIdx.x >= info[4]) return;
+  }
   if (wk.y == wk.z) {  // an empty tile (uniform): only the background shows
     const BinInfo bi = decode_bin(P, wk.x);
     const int lth = 8 - P.ltw;
@@ -1813,7 +1822,7 @@ __global__ __launch_bounds__(256) void k_fwd_fine(
         }
         packed |= m << (5 * c);
       }
-      kslot[size_t(blockIdx.x) * TP + t] = packed;
+      if (!P.coarser) kslot[size_t(blockIdx.x) * TP + t] = packed;
     }
     // blend front to back
     const uint32_t k = min(cnt, uint32_t(KEEP));
@@ -3938,7 +3947,7 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
     {  // one workgroup per work item (the longer path, enqueued first); workgroups beyond the
        // item count exit at once
       StageTimer tm(ST_FWD_ITEMS, st);
-      if (uint64_t(P.n) * uint64_t(P.V) <= SELECT_POINTS && !P.coarser)
+      if (uint64_t(P.n) * uint64_t(P.V) <= SELECT_POINTS)
         hipLaunchKernelGGL(k_fwd_select<D>, dim3(uint32_t(lay.icap)), dim3(FI_T), 0, st, P, info,
                            work, ent, pts.desc, pyr, npix, kkey, kgam, pcnt, pkey, pgam, X.bg,
                            X.alpha);
@@ -3951,8 +3960,8 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
     hipError_t e0 = hipStreamWaitEvent(sd->s, sd->fork, 0);
     {  // one workgroup per fine tile; workgroups beyond their count exit at once
       StageTimer tm(ST_FWD_FINE, sd->s);
-      hipLaunchKernelGGL(k_fwd_fine<D>, dim3(P.NB), dim3(256), 0, sd->s, P, info, fine_work, ent,
-                         kslot, pts.desc, pyr, npix, kkey, kgam, X.bg, X.alpha);
+      hipLaunchKernelGGL(k_fwd_fine<D>, dim3(P.NB), dim3(256), 0, sd->s, P, info, fine_work,
+                         bin_start, ent, kslot, pts.desc, pyr, npix, kkey, kgam, X.bg, X.alpha);
     }
     hipError_t e1 = hipGetLastError();
     hipError_t e2 = hipEventRecord(sd->join, sd->s);
