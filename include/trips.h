@@ -16,8 +16,8 @@
  *    that returns an error launched nothing.  HIP launch failures return
  *    TRIPS_ERR_HIP and the HIP error code is kept for trips_last_hip_error().
  *  - All work is enqueued on `stream` in order; results are ready when the stream is.
- *    Part of a forward or backward call (the kernels of the tiles with few entries) runs on
- *    a second stream of the device that the library creates once, with the default
+ *    Part of a forward or backward call (the kernels of the tiles with few entries), except
+ *    in uncaptured calls of a few thousand points, runs on a second stream of the device that the library creates once, with the default
  *    priority, forked from `stream` and joined back into it within the call; captured into
  *    a graph, the two become branches of it.
  *  - Up to TRIPS_MAX_VIEWS views of arbitrary, different resolutions are rendered by

@@ -3807,8 +3807,8 @@ trips_status static_scratch(void*& out) {
 }
 
 // A second stream per device for the fine-tile kernels, which touch other tiles than the
-// work-item kernels and run beside them (a fork and a join on the caller's stream; in a
-// captured plan these become two branches of the graph).  Created on first use with the
+// work-item kernels and run beside them (side_by_side: a fork and a join on the caller's stream;
+// in a captured plan these become two branches of the graph).  Created on first use with the
 // default priority and kept until the process ends; g_side_launch serialises the calls that
 // use it, so the fork and join events of one call are never interleaved with another's.
 struct SideStream {
@@ -3836,6 +3836,49 @@ trips_status side_stream(SideStream*& out) {
     sd.s = s;
   }
   out = &sd;
+  return TRIPS_OK;
+}
+
+// Enqueues first(stream) and beside(stream), two kernels that may run at the same time, then
+// after(stream), which needs the first and lies beside the other like it.  The second goes to the
+// side stream between a fork and a join.  These cost six calls of the runtime and two waits of
+// 5-10 us, so outside a capture kernels of a few microseconds (in_line) simply follow each other:
+// forward of 300 points 52 against 24 us, forward + backward of 4096 points 115 against 78.  The
+// line lies where the waits become shorter than the overlap: at 640x480 the forward of 8k points
+// takes 79 us forked and 85 in line, the backward of 8k 86 and 28, of 32k 37 and 40.  In a graph
+// the branches cost no calls and are the faster form at 4096 points too (75 against 80 us).
+constexpr uint64_t IN_LINE_FWD = 4096, IN_LINE_BWD = 16384;  // (point, view) pairs
+template <class F, class B, class A>
+trips_status side_by_side(bool in_line, hipStream_t st, F&& first, B&& beside, A&& after) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (in_line) TRIPS_HIP(hipStreamIsCapturing(st, &cs));
+  if (in_line && cs == hipStreamCaptureStatusNone) {
+    first(st);
+    beside(st);
+    after(st);
+    TRIPS_HIP(hipGetLastError());
+    return TRIPS_OK;
+  }
+  SideStream* sd = nullptr;
+  const trips_status ss = side_stream(sd);
+  if (ss != TRIPS_OK) return ss;
+  std::lock_guard<std::mutex> lk(g_side_launch);
+  TRIPS_HIP(hipEventRecord(sd->fork, st));
+  first(st);
+  const hipError_t e0 = hipGetLastError();
+  const hipError_t e1 = hipStreamWaitEvent(sd->s, sd->fork, 0);
+  beside(sd->s);
+  const hipError_t e2 = hipGetLastError();
+  const hipError_t e3 = hipEventRecord(sd->join, sd->s);
+  after(st);
+  const hipError_t e4 = hipGetLastError();
+  // the join is enqueued whatever failed, so a captured graph has no dangling branch
+  TRIPS_HIP(hipStreamWaitEvent(st, sd->join, 0));
+  TRIPS_HIP(e0);
+  TRIPS_HIP(e1);
+  TRIPS_HIP(e2);
+  TRIPS_HIP(e3);
+  TRIPS_HIP(e4);
   return TRIPS_OK;
 }
 
@@ -3938,46 +3981,33 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
     TRIPS_HIP(hipGetLastError());
   }
   {
-    // the fine tiles on the side stream, beside the work items and their merge
-    SideStream* sd = nullptr;
-    trips_status ss = side_stream(sd);
-    if (ss != TRIPS_OK) return ss;
-    std::lock_guard<std::mutex> lk(g_side_launch);
-    TRIPS_HIP(hipEventRecord(sd->fork, st));
-    {  // one workgroup per work item (the longer path, enqueued first); workgroups beyond the
-       // item count exit at once
-      StageTimer tm(ST_FWD_ITEMS, st);
-      if (uint64_t(P.n) * uint64_t(P.V) <= SELECT_POINTS)
-        hipLaunchKernelGGL(k_fwd_select<D>, dim3(uint32_t(lay.icap)), dim3(FI_T), 0, st, P, info,
-                           work, ent, pts.desc, pyr, npix, kkey, kgam, pcnt, pkey, pgam, X.bg,
-                           X.alpha);
-      else
-        hipLaunchKernelGGL(k_fwd_items<D>, dim3(uint32_t(lay.icap)), dim3(256), 0, st, P, info,
-                           work, bin_start, item_start, ent, pts.desc, pyr, npix, kkey, kgam, pcnt,
-                           pkey, pgam, X.bg, X.alpha);
-    }
-    hipError_t e3 = hipGetLastError();
-    hipError_t e0 = hipStreamWaitEvent(sd->s, sd->fork, 0);
-    {  // one workgroup per fine tile; workgroups beyond their count exit at once
-      StageTimer tm(ST_FWD_FINE, sd->s);
-      hipLaunchKernelGGL(k_fwd_fine<D>, dim3(P.NB), dim3(256), 0, sd->s, P, info, fine_work,
-                         bin_start, ent, kslot, pts.desc, pyr, npix, kkey, kgam, X.bg, X.alpha);
-    }
-    hipError_t e1 = hipGetLastError();
-    hipError_t e2 = hipEventRecord(sd->join, sd->s);
-    if (P.n > int64_t(P.item_e)) {  // (a tile has at most one entry per point)
-      StageTimer tm(ST_FWD_MERGE, st);
-      hipLaunchKernelGGL(k_fwd_merge<D>, dim3(1024), dim3(256), 0, st, P, item_start, multi_bins,
-                         info, pcnt, pkey, pgam, pts.desc, pyr, npix, kkey, kgam, X.bg, X.alpha);
-    }
-    hipError_t e4 = hipGetLastError();
-    // the join is enqueued whatever failed, so a captured graph has no dangling branch
-    TRIPS_HIP(hipStreamWaitEvent(st, sd->join, 0));
-    TRIPS_HIP(e0);
-    TRIPS_HIP(e1);
-    TRIPS_HIP(e2);
-    TRIPS_HIP(e3);
-    TRIPS_HIP(e4);
+    // the fine tiles beside the work items
+    const trips_status bs = side_by_side(
+        uint64_t(P.n) * uint64_t(P.V) <= IN_LINE_FWD, st,
+        [&](hipStream_t q) {  // one workgroup per work item (the longer path, enqueued first);
+                              // workgroups beyond the item count exit at once
+          StageTimer tm(ST_FWD_ITEMS, q);
+          if (uint64_t(P.n) * uint64_t(P.V) <= SELECT_POINTS)
+            hipLaunchKernelGGL(k_fwd_select<D>, dim3(uint32_t(lay.icap)), dim3(FI_T), 0, q, P, info,
+                               work, ent, pts.desc, pyr, npix, kkey, kgam, pcnt, pkey, pgam, X.bg,
+                               X.alpha);
+          else
+            hipLaunchKernelGGL(k_fwd_items<D>, dim3(uint32_t(lay.icap)), dim3(256), 0, q, P, info,
+                               work, bin_start, item_start, ent, pts.desc, pyr, npix, kkey, kgam,
+                               pcnt, pkey, pgam, X.bg, X.alpha);
+        },
+        [&](hipStream_t q) {  // one workgroup per fine tile; those beyond their count exit at once
+          StageTimer tm(ST_FWD_FINE, q);
+          hipLaunchKernelGGL(k_fwd_fine<D>, dim3(P.NB), dim3(256), 0, q, P, info, fine_work, bin_start,
+                             ent, kslot, pts.desc, pyr, npix, kkey, kgam, X.bg, X.alpha);
+        },
+        [&](hipStream_t q) {
+          if (P.n <= int64_t(P.item_e)) return;  // (a tile has at most one entry per point)
+          StageTimer tm(ST_FWD_MERGE, q);
+          hipLaunchKernelGGL(k_fwd_merge<D>, dim3(1024), dim3(256), 0, q, P, item_start, multi_bins,
+                             info, pcnt, pkey, pgam, pts.desc, pyr, npix, kkey, kgam, X.bg, X.alpha);
+        });
+    if (bs != TRIPS_OK) return bs;
   }
   if (P.coarser) {  // coarsest layer first: each layer merges the blended lists above it
     StageTimer tm(ST_INCL_FWD, st);
@@ -4071,33 +4101,23 @@ trips_status launch_backward(const Layout& lay, const trips_points& pts, const f
     }
     TRIPS_HIP(hipGetLastError());
   } else {
-    // the fine tiles on the side stream, beside the blend adjoints and rows of the items
-    SideStream* sd = nullptr;
-    trips_status ss = side_stream(sd);
-    if (ss != TRIPS_OK) return ss;
-    std::lock_guard<std::mutex> lk(g_side_launch);
-    TRIPS_HIP(hipEventRecord(sd->fork, st));
-    {  // the longer path first
-      StageTimer tm(ST_BWD_ITEMS, st);
-      hipLaunchKernelGGL((k_bwd_items<D, false, 512>),
-                         dim3(std::min<uint32_t>(uint32_t(lay.icap), BWD_GRID)), dim3(512), 0, st, P,
-                         info, work, bin_start, ent, npix, kkey, kgam, pts.desc, gpyr, rows, kept,
-                         nullptr, nullptr, X);
-    }
-    hipError_t e3 = hipGetLastError();
-    hipError_t e0 = hipStreamWaitEvent(sd->s, sd->fork, 0);
-    {
-      StageTimer tm(ST_BWD_FINE, sd->s);
-      hipLaunchKernelGGL(k_bwd_fine<D>, dim3(P.NB), dim3(256), 0, sd->s, P, info, fine_work, ent,
-                         kslot, npix, pts.desc, gpyr, rows, kept, X);
-    }
-    hipError_t e1 = hipGetLastError();
-    hipError_t e2 = hipEventRecord(sd->join, sd->s);
-    TRIPS_HIP(hipStreamWaitEvent(st, sd->join, 0));
-    TRIPS_HIP(e0);
-    TRIPS_HIP(e1);
-    TRIPS_HIP(e2);
-    TRIPS_HIP(e3);
+    // the fine tiles beside the work items
+    const trips_status bs = side_by_side(
+        uint64_t(P.n) * uint64_t(P.V) <= IN_LINE_BWD, st,
+        [&](hipStream_t q) {
+          StageTimer tm(ST_BWD_ITEMS, q);
+          hipLaunchKernelGGL((k_bwd_items<D, false, 512>),
+                             dim3(std::min<uint32_t>(uint32_t(lay.icap), BWD_GRID)), dim3(512), 0, q,
+                             P, info, work, bin_start, ent, npix, kkey, kgam, pts.desc, gpyr, rows,
+                             kept, nullptr, nullptr, X);
+        },
+        [&](hipStream_t q) {
+          StageTimer tm(ST_BWD_FINE, q);
+          hipLaunchKernelGGL(k_bwd_fine<D>, dim3(P.NB), dim3(256), 0, q, P, info, fine_work, ent, kslot,
+                             npix, pts.desc, gpyr, rows, kept, X);
+        },
+        [](hipStream_t) {});
+    if (bs != TRIPS_OK) return bs;
   }
   if (P.n > 0) {
     StageTimer tm(ST_BWD_POINTS, st);
