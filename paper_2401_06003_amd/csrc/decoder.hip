@@ -18,12 +18,19 @@
 //    ceil(9 D / 32) steps over (tap, layer channel), so every A fragment is one or two
 //    LDS reads at 16-byte granularity; B fragments are stored lane-major (packed once by
 //    k_dec_pack) and read without bank conflicts;
-//  - a wave owns four rows of the tile: 4 x 4 accumulator tiles of 16 outputs x 16 texels
+//  - a wave owns four (or two) rows of the tile: 4 x 4 accumulator tiles of 16 outputs x 16 texels
 //    (kernel fragments as the A operand); outputs 16j + 4(lane/16) + i (feature, j = 0, 1)
 //    and 32 + the same (gate) of texel lane%16 sit in the same lane, so the gating needs no
 //    exchange and every lane reads and writes four consecutive channels at once;
 //  - the epilogue gates, adds the bypass, rounds to binary16 and writes the tile through LDS
 //    in 16-byte rows (or applies the output layer and writes float32).
+// Bound by the vector ALU (two thirds of its cycles at layer 0: doubling, gating, addresses; the
+// matrix cores are busy a third of the time) and, on layers of few tiles, by the latency of a tile.
+// There eight waves of two rows each shorten the tile's chain (a layer of one tile to a few per CU
+// takes 8 us instead of 9.5); with many tiles per CU four waves of four rows read the kernel
+// fragments half as often (layer 0 of 1920x1080 150 us against 160).  Halos inside the layer skip
+// the zeroing.  The network at 1920x1080, 8 layers, D = 4: 237 -> 229 us; 643x477, 5 layers, D = 8:
+// 68 -> 62 us; 100x70: 23.5 -> 21.2 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -47,7 +54,6 @@ constexpr int HPIX = HALO * HALO;         // 324 halo texels
 constexpr int PSTRIDE = 40;               // halves per halo texel: 32 doubled + 8 layer channels
 constexpr int CREG = TILE / 2 + 2;        // coarser texels under the halo, per row and column
 constexpr int OSTRIDE = 40;               // halves per texel of the output staging (32 used)
-constexpr int DEC_THREADS = 256;
 constexpr int MAX_OUT = 8;
 constexpr int MAXL = TRIPS_MAX_LAYERS;
 
@@ -163,13 +169,21 @@ __device__ __forceinline__ void up_taps(int i, int n, int& near, int& far) {
 
 // FO: 0 = write the block output; 3 = apply a 3-channel output layer; MAX_OUT = apply an
 // output layer of out_dim <= MAX_OUT channels (zero padded)
-template <int D, bool COARSE, int FO>
-__global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
+// RPW: tile rows per wavefront (4 or 2, so 256 or 512 threads)
+template <int D, bool COARSE, int FO, int RPW>
+__global__ __launch_bounds__(64 * (TILE / RPW), 8 / RPW) void k_dec_block(
     const float* __restrict__ feat, const uint16_t* __restrict__ coarse,
     const uint16_t* __restrict__ packed, const float* __restrict__ outw, int W, int H, int Wc,
     int Hc, int out_dim, uint16_t* __restrict__ hout, float* __restrict__ image) {
   constexpr int STEPS = conv_steps(D, COARSE);
   constexpr int S0 = COARSE ? 9 : 0;
+  constexpr int DEC_THREADS = 64 * (TILE / RPW);
+  constexpr int NL = (CREG * CREG * 4 + DEC_THREADS - 1) / DEC_THREADS;  // loads per thread
+  static_assert(HPIX <= NL * DEC_THREADS, "the halo too");
+  // channels of a unit of the doubling: 200 units of eight or 400 of four fill the threads
+  constexpr int UC = RPW == 4 ? 8 : 4;
+  typedef _Float16 halfu __attribute__((ext_vector_type(UC)));
+  typedef uint32_t wordu __attribute__((ext_vector_type(UC / 2)));
   // B fragments; of the last step only lanes 0..15 hold K indices below 9 D (both for D = 4
   // and D = 8), so only those are staged
   __shared__ __align__(16) half8 s_b[(STEPS - 1) * 4 * 64 + 4 * 16];
@@ -178,8 +192,8 @@ __global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
   __shared__ float s_bias[NOUT];
   constexpr bool FINAL = FO > 0;
   __shared__ float s_ow[FINAL ? (FEAT + 1) * FO : 1];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   {  // the packed kernel, once per workgroup
+    const int t = threadIdx.x;
     const uint4* src = reinterpret_cast<const uint4*>(packed);
     uint4* dst = reinterpret_cast<uint4*>(s_b);
     for (int i = t; i < (STEPS - 1) * 256; i += DEC_THREADS) dst[i] = src[i];
@@ -200,13 +214,13 @@ __global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
   // tile's while this one is on the matrix cores).  The coarser block's texels under the
   // halo (rows and columns (y0 >> 1) - 1 .. + CREG - 1, clamped to the layer on load) go to
   // LDS as they are; the layer's features go to the halo as binary16.
-  half8 cv[2];
-  float4 fv[2][D / 4];
-  auto fetch = [&](int tile) {
+  half8 cv[NL];
+  float4 fv[NL][D / 4];
+  auto fetch = [&](int tile, int t) {
     const int y0 = (tile / tx_n) * TILE, x0 = (tile % tx_n) * TILE;
     const int cy0 = (y0 >> 1) - 1, cx0 = (x0 >> 1) - 1;
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
+    for (int r = 0; r < NL; ++r) {
       const int u = t + r * DEC_THREADS;
       if (COARSE && u < CREG * CREG * 4) {
         const int p = u >> 2, g = u & 3;
@@ -224,13 +238,18 @@ __global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
       }
     }
   };
-  if (int(blockIdx.x) < tiles) fetch(blockIdx.x);
+  if (int(blockIdx.x) < tiles) fetch(blockIdx.x, threadIdx.x);
   for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    // (with half the registers, the empty asm keeps what depends on the thread alone from being
+    // held in them across tiles)
+    int t = threadIdx.x;
+    if (RPW == 2) asm volatile("" : "+v"(t));
+    const int lane = t & 63, wave = t >> 6;
     const int y0 = (tile / tx_n) * TILE, x0 = (tile % tx_n) * TILE;
     const int cy0 = (y0 >> 1) - 1, cx0 = (x0 >> 1) - 1;
     __syncthreads();  // previous tile's staging is consumed (and the kernel is in LDS)
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
+    for (int r = 0; r < NL; ++r) {
       const int u = t + r * DEC_THREADS;
       if (COARSE && u < CREG * CREG * 4) s_c[u] = cv[r];
       if (u < HPIX) {
@@ -256,16 +275,19 @@ __global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
     // texels outside the halo, which are skipped.
     if (COARSE) {
       constexpr int CP = CREG / 2;  // column pairs
-      for (int u = t; u < CREG * CP * 4; u += DEC_THREADS) {
-        const int g = u & 3, q = u >> 2, ur = q / CP, uc2 = q % CP;
-        half8 cr[3][4];
+      // (uniform) the whole halo lies in the layer: no texel of it is zeroed
+      const bool inside = y0 > 0 && x0 > 0 && y0 + TILE < H && x0 + TILE < W;
+      constexpr int UG = FEAT / UC;
+      for (int u = t; u < CREG * CP * UG; u += DEC_THREADS) {
+        const int g = u % UG, q = u / UG, ur = q / CP, uc2 = q % CP;
+        halfu cr[3][4];
 #pragma unroll
         for (int a2 = 0; a2 < 3; ++a2)
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             const int ry = min(max(ur - 1 + a2, 0), CREG - 1);
             const int rx = min(max(2 * uc2 - 1 + j, 0), CREG - 1);
-            cr[a2][j] = s_c[(ry * CREG + rx) * 4 + g];
+            cr[a2][j] = reinterpret_cast<const halfu*>(s_c)[(ry * CREG + rx) * UG + g];
           }
         // 3/4 near + 1/4 far is (3 near + far) / 4, and a power-of-two scale is exact: each
         // pass forms 3 near + far with one rounding (from the binary16 values directly along
@@ -274,11 +296,11 @@ __global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
 #pragma unroll
         for (int dy = 0; dy < 2; ++dy) {
           // even layer row (dy = 0): far row above; odd (dy = 1): far row below
-          float v[4][8];
+          float v[4][UC];
 #pragma unroll
           for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int e = 0; e < UC; ++e)
               v[j][e] = fmaf(3.0f, float(cr[1][j][e]), float(cr[dy ? 2 : 0][j][e]));
 #pragma unroll
           for (int w = 0; w < 2; ++w) {  // coarser column 2 uc2 + w: near j = 1 + w
@@ -286,35 +308,38 @@ __global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
             for (int dx = 0; dx < 2; ++dx) {  // far column j = w (dx = 0) or 2 + w (dx = 1)
               const int hy = 2 * ur - 1 + dy, hx = 2 * (2 * uc2 + w) - 1 + dx;
               if (hy < 0 || hy >= HALO || hx < 0 || hx >= HALO) continue;
-              const int y = y0 - 1 + hy, x = x0 - 1 + hx;
-              const bool inimg = y >= 0 && y < H && x >= 0 && x < W;
-              half8 hv;
+              halfu hv;
 #pragma unroll
-              for (int e = 0; e < 8; ++e)
+              for (int e = 0; e < UC; ++e)
                 hv[e] = _Float16(0.0625f * fmaf(3.0f, v[1 + w][e], v[dx ? 2 + w : w][e]));
-              uint4 hw = *reinterpret_cast<const uint4*>(&hv);
-              hw.x = inimg ? hw.x : 0u; hw.y = inimg ? hw.y : 0u;
-              hw.z = inimg ? hw.z : 0u; hw.w = inimg ? hw.w : 0u;
-              reinterpret_cast<uint4*>(s_in + (hy * HALO + hx) * PSTRIDE)[g] = hw;
+              wordu hw = *reinterpret_cast<const wordu*>(&hv);
+              if (!inside) {
+                const int y = y0 - 1 + hy, x = x0 - 1 + hx;
+                const bool inimg = y >= 0 && y < H && x >= 0 && x < W;
+#pragma unroll
+                for (int e = 0; e < UC / 2; ++e) hw[e] = inimg ? hw[e] : 0u;
+              }
+              reinterpret_cast<wordu*>(s_in + (hy * HALO + hx) * PSTRIDE)[g] = hw;
             }
           }
         }
       }
     }
     __syncthreads();
-    if (tile + int(gridDim.x) < tiles) fetch(tile + gridDim.x);  // in flight during the MFMAs
-    // ---- implicit GEMM: wave owns tile rows 4 wave .. 4 wave + 3
+    if (tile + int(gridDim.x) < tiles) fetch(tile + gridDim.x, t);  // in flight during the MFMAs
+    // ---- implicit GEMM: a wave owns RPW rows of the tile
     // The kernel fragments go in as the A operand and the texels as B, so the accumulator is
     // the transposed tile: lane (grp, col) holds outputs 16 j + 4 grp + i of texel col.
     const int col = lane & 15, grp = lane >> 4;
-    floatx4 acc[4][4];
+    const int row0 = RPW * wave;
+    floatx4 acc[RPW][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       floatx4 bj;
 #pragma unroll
       for (int i = 0; i < 4; ++i) bj[i] = s_bias[16 * j + 4 * grp + i];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[r][j] = bj;
+      for (int r = 0; r < RPW; ++r) acc[r][j] = bj;
     }
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
@@ -333,8 +358,8 @@ __global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
         }
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 4 * wave + r;
+      for (int r = 0; r < RPW; ++r) {
+        const int row = row0 + r;
         half8 a;
         if (s < S0) {  // tap s, doubled channels 8 grp .. 8 grp + 7
           const int dy = s / 3, dx = s % 3;
@@ -373,10 +398,10 @@ __global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
     }
     // ---- epilogue: lane holds outputs 16 j + 4 grp + i (features j = 0, 1; gates j + 2) of
     // texel (row, col): four consecutive channels, read and written as 8-byte pieces
-    half4 hv[4][2];
+    half4 hv[RPW][2];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = 4 * wave + r;
+    for (int r = 0; r < RPW; ++r) {
+      const int row = row0 + r;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         half4 up;
@@ -394,10 +419,10 @@ __global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
     __syncthreads();  // every wave is done with the halo; it becomes the output staging
     _Float16* s_out = s_in;  // [256 texels][OSTRIDE]: texels 80 bytes apart hit other banks
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < RPW; ++r)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        *reinterpret_cast<half4*>(s_out + ((4 * wave + r) * TILE + col) * OSTRIDE + 16 * j +
+        *reinterpret_cast<half4*>(s_out + ((row0 + r) * TILE + col) * OSTRIDE + 16 * j +
                                   4 * grp) = hv[r][j];
     __syncthreads();
     if (!FINAL) {  // 16-byte pieces: four per texel, tile rows contiguous in memory
@@ -408,14 +433,16 @@ __global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
           reinterpret_cast<uint4*>(hout)[(size_t(y) * W + x) * 4 + g] =
               *reinterpret_cast<const uint4*>(s_out + p * OSTRIDE + 8 * g);
       }
-    } else {  // the output layer, one texel per thread (weights from LDS, FO-padded)
+    } else if (t < TILE * TILE) {  // the output layer, one texel per thread (weights from LDS,
+                                   // FO-padded)
       const int y = y0 + t / TILE, x = x0 + t % TILE;
       if (y < H && x < W) {
         float o[FINAL ? FO : 1];
 #pragma unroll
         for (int k = 0; k < FO; ++k) o[k] = s_ow[FEAT * FO + k];
         const half8* hp = reinterpret_cast<const half8*>(s_out + t * OSTRIDE);
-        constexpr int CU = FO == 3 ? FEAT / 8 : 1;  // (the generic width stays rolled)
+        // (the generic width, and with half the registers, stays rolled)
+        constexpr int CU = FO == 3 && RPW == 4 ? FEAT / 8 : 1;
 #pragma unroll CU
         for (int c8 = 0; c8 < FEAT / 8; ++c8) {
           const half8 hv8 = hp[c8];
@@ -443,15 +470,17 @@ __global__ __launch_bounds__(DEC_THREADS, 2) void k_dec_block(
 
 bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Workgroups of one block launch: one per tile up to two per CU (the residency the kernel's
-// LDS allows), each looping over tiles with the layer's packed kernel staged once.
-uint32_t dec_grid(int W, int H) {
-  const uint32_t tiles = uint32_t((W + TILE - 1) / TILE) * uint32_t((H + TILE - 1) / TILE);
+uint32_t dec_cus() {
   int dev = 0, cus = 256;
   if (hipGetDevice(&dev) == hipSuccess)
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  return std::min<uint32_t>(tiles, 2u * uint32_t(std::max(cus, 1)));
+  return uint32_t(std::max(cus, 1));
 }
+
+// Layers of at most FEW_TILES tiles per CU take the eight-wave form (643x477, 4.8 tiles per CU at
+// layer 0: 62 us against 64 in the four-wave form; at 8 per CU, layer 1 of 1920x1080, the network
+// takes 229 us with the four-wave form there and 238 with the other).
+constexpr uint32_t FEW_TILES = 6;
 
 template <int D>
 trips_status launch_block(const DecLayout& d, const char* packed, int L, const float* feat,
@@ -462,11 +491,22 @@ trips_status launch_block(const DecLayout& d, const char* packed, int L, const f
   const float* ow = reinterpret_cast<const float*>(packed + d.out_off);
   const int W = d.W[L], H = d.H[L];
   const int Wc = has_coarse ? d.W[L + 1] : 1, Hc = has_coarse ? d.H[L + 1] : 1;
-  const dim3 grid(dec_grid(W, H)), blk(DEC_THREADS);
+  const uint32_t cus = dec_cus();
+  const uint32_t tiles = uint32_t((W + TILE - 1) / TILE) * uint32_t((H + TILE - 1) / TILE);
+  // one workgroup per tile up to two per CU (the residency the kernel's LDS allows), each looping
+  // over tiles with the layer's packed kernel staged once
+  const dim3 grid(std::min(tiles, 2u * cus));
+  const bool few = tiles <= FEW_TILES * cus;
   const int fo = image ? (d.out_dim == 3 ? 3 : MAX_OUT) : 0;
 #define DEC_LAUNCH(C, F)                                                                   \
-  hipLaunchKernelGGL((k_dec_block<D, C, F>), grid, blk, 0, st, feat, coarse, pk, ow, W, H, \
-                     Wc, Hc, d.out_dim, hout, image)
+  do {                                                                                     \
+    if (few)                                                                               \
+      hipLaunchKernelGGL((k_dec_block<D, C, F, 2>), grid, dim3(512), 0, st, feat, coarse,  \
+                         pk, ow, W, H, Wc, Hc, d.out_dim, hout, image);                    \
+    else                                                                                   \
+      hipLaunchKernelGGL((k_dec_block<D, C, F, 4>), grid, dim3(256), 0, st, feat, coarse,  \
+                         pk, ow, W, H, Wc, Hc, d.out_dim, hout, image);                    \
+  } while (0)
   if (has_coarse) {
     if (fo == 3) DEC_LAUNCH(true, 3);
     else if (fo) DEC_LAUNCH(true, MAX_OUT);

@@ -94,6 +94,32 @@ def test_output_layer(gpu, D):
     assert np.all(np.abs(got - ref) <= bar)
 
 
+@pytest.mark.parametrize("gate", [-300.0, -95.0, 95.0, 300.0])
+def test_saturated_gates(gpu, gate):
+    """Gate pre-activations beyond the range of the float32 exponential, on tiles inside the
+    layer and at its border: the block's output is the bypass (closed) or the bypass plus the
+    ELU (open), as the oracle gives it, with the bars of test_block_parity."""
+    import torch
+    import paper_2401_06003_amd as tp
+    W, H, D = 52, 50, 4
+    wt = scenes.decoder_weights(61, 2, D)
+    wt["b"][0] = wt["b"][0].copy()
+    wt["b"][0][F:] = gate
+    d = tp.Decoder(W, H, 2, D, wt, device=gpu)
+    rng = np.random.default_rng(62)
+    feat = rng.uniform(0, 1, (H, W, D)).astype(np.float32)
+    Wc, Hc = d.dims[1]
+    coarse = rng.uniform(-0.5, 1.5, (Hc, Wc, F)).astype(np.float16)
+    got = d.block(0, torch.from_numpy(feat).to(gpu), torch.from_numpy(coarse).to(gpu))
+    got = got.cpu().numpy().astype(np.float64)
+    ref = dec.block(feat, coarse, wt["w"][0], wt["b"][0], fp16=True)
+    up = dec.r16(dec.upsample2(coarse, H, W))
+    x = np.concatenate([dec.r16(feat), up], axis=2)
+    bar = _block_bar(np.abs(x), wt["w"][0], wt["b"][0], ref)
+    bar += np.spacing(np.abs(up).astype(np.float16)).astype(np.float64)
+    assert np.isfinite(got).all() and np.all(np.abs(got - ref) <= bar)
+
+
 def _net_check(img, ref):
     scale = np.abs(ref).mean()
     err = np.abs(img - ref)
