@@ -75,3 +75,12 @@ def test_lists_selected_by_counting(gpu, n, W, H, nl, item, ties):
     sc = scenes.random_small(40, n=n, W=W, H=H, nlayers=nl, s_lo=0.4, s_hi=10.0, depth_ties=ties)
     r = _check(sc, gpu, tp.make_tuning(16, 0, item))
     assert r.tile_stats()[0].max() > 300
+
+
+@pytest.mark.parametrize("n,D", [(3000, 4), (5000, 4), (5000, 8)])
+def test_points_with_more_than_four_entries(gpu, n, D):
+    """Tiles of 8 texels: one point in some forty crosses a tile corner in one of its layers and
+    has five to eight entries; binned by one workgroup and by four passes."""
+    import paper_2401_06003_amd as tp
+    sc = scenes.random_small(50, n=n, W=96, H=80, nlayers=4, D=D, s_lo=0.5, s_hi=8.0)
+    _check(sc, gpu, tp.make_tuning(8, 0, 0))
