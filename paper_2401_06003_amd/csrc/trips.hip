@@ -2488,17 +2488,25 @@ constexpr int PT = TP / 4;  // covering texels of one tile in the next coarser l
 
 // incl_fwd: one launch per layer, coarsest first; one workgroup per tile of the layer
 // (grid.y = view).  The coarsest layer's blended list is its own (copied); every finer
-// texel merges its own list (staged in LDS) with its covering texel's blended list
-// (the tile's 64 covering texels staged in LDS), blends the result (Eq. 6-7) and rewrites
-// its outputs.
+// texel merges its own list (its first INCL_OWN fragments staged in LDS) with its covering
+// texel's blended list (the tile's 64 covering texels staged in LDS), blends the result (Eq. 6-7)
+// and rewrites its outputs.
+// A chain of dependent loads (counts, keys, merge, descriptors), so bound by how many workgroups
+// a CU holds to hide it: with all 16 own fragments staged the LDS (62 KB) held two, and layers 0
+// and 1 of a 1920x1080 view took 200 us; eight (37 KB) let four in, with the registers to match,
+// and take 121 us (four staged: 117 us, but the finer layers of dense clouds then read more of
+// their own lists one by one).  Five workgroups spill registers.  Staging the covering lists'
+// descriptors as well, which saves three quarters of the gathers, is slower: 16 KB of LDS and one
+// more dependent load.
+constexpr int INCL_OWN = 8;
 template <int D>
-__global__ __launch_bounds__(256) void k_incl_fwd(
+__global__ __launch_bounds__(256, 4) void k_incl_fwd(
     const Params P, int L, const uint32_t* __restrict__ npix, const uint64_t* __restrict__ kkey,
     const float* __restrict__ kgam, uint64_t* __restrict__ fkey, float* __restrict__ fgam,
     uint32_t* __restrict__ fcnt, const float* __restrict__ desc, float* __restrict__ pyr,
     const float* __restrict__ bg, float* __restrict__ alpha) {
-  __shared__ uint64_t s_ok[KEEP][TP];
-  __shared__ float s_og[KEEP][TP];
+  __shared__ uint64_t s_ok[INCL_OWN][TP];
+  __shared__ float s_og[INCL_OWN][TP];
   __shared__ uint64_t s_pk[KEEP][PT];
   __shared__ float s_pg[KEEP][PT];
   __shared__ uint32_t s_pn[PT];
@@ -2534,10 +2542,10 @@ __global__ __launch_bounds__(256) void k_incl_fwd(
     return;
   }
   // slots are staged whatever the list length (stale values past it are never read), so
-  // their loads do not wait on one another: all 16 in the coarser layers, the first four in
-  // the two finest (longer own lists are rare there and load the rest)
+  // their loads do not wait on one another: all INCL_OWN in the coarser layers, the first four
+  // in the two finest (longer own lists are rare there and load the rest)
 #pragma unroll
-  for (int m = 0; m < KEEP; ++m) {
+  for (int m = 0; m < INCL_OWN; ++m) {
     if (m < 4 || L >= 2 || uint32_t(m) < ko) {
       s_ok[m][t] = kkey[(tb + m) * TP + t];
       s_og[m][t] = kgam[(tb + m) * TP + t];
@@ -2574,12 +2582,17 @@ __global__ __launch_bounds__(256) void k_incl_fwd(
   float fg[KEEP];
 #pragma unroll
   for (int m = 0; m < KEEP; ++m) {
-    const uint64_t ok = io < ko ? s_ok[min(io, uint32_t(KEEP - 1))][t] : KEY_NONE;
+    uint64_t ok = io < ko ? s_ok[min(io, uint32_t(INCL_OWN - 1))][t] : KEY_NONE;
+    float og = s_og[min(io, uint32_t(INCL_OWN - 1))][t];
+    if (m >= INCL_OWN && io >= uint32_t(INCL_OWN) && io < ko) {  // past the staged fragments
+      ok = kkey[(tb + io) * TP + t];
+      og = kgam[(tb + io) * TP + t];
+    }
     const uint64_t pk = ip < kp ? s_pk[min(ip, uint32_t(KEEP - 1))][q] : KEY_NONE;
     const bool take_o = io < ko && !(pk < ok);
     const bool take_p = !take_o && ip < kp;
     fk[m] = take_o ? ok : (take_p ? pk : KEY_NONE);
-    fg[m] = take_o ? s_og[min(io, uint32_t(KEEP - 1))][t]
+    fg[m] = take_o ? og
                    : (take_p ? s_pg[min(ip, uint32_t(KEEP - 1))][q] : 0.0f);
     mask |= (take_p ? 1u : 0u) << m;
     io += take_o ? 1u : 0u;
@@ -2641,8 +2654,12 @@ __global__ __launch_bounds__(256) void k_incl_fwd(
 // that tile form a (tw >> k) x (th >> k) block that lies over no other tile of layer Lb, so
 // the workgroup runs the layers itself, coarsest first, with a barrier between layers: each
 // layer merges and blends exactly as k_incl_fwd does, stores its blended lists, and hands
-// them to the next finer layer through LDS.  Layer Lt reads its covering lists (layer Lt + 1,
-// an earlier launch) from memory; the coarsest layer of the pyramid keeps its own lists.
+// them to the next finer layer through LDS.  Layer Lt > Lb reads its covering lists (layer Lt + 1,
+// an earlier launch) from memory, every texel (at most PT) a copy of its own; the coarsest layer
+// of the pyramid keeps its own lists.
+// Bound by the chain of one layer after another.  Both lists of a merge are indexed in LDS:
+// picking their next items out of registers, 32 selects per step, took layers 2-6 of a
+// 1920x1080 view 51 us instead of 43.
 template <int D>
 __global__ __launch_bounds__(256) void k_incl_fwd_group(
     const Params P, int Lb, int Lt, const uint32_t* __restrict__ npix,
@@ -2652,6 +2669,8 @@ __global__ __launch_bounds__(256) void k_incl_fwd_group(
   __shared__ uint64_t s_k[2][KEEP][PT];  // blended lists of a layer's block, for the next layer
   __shared__ float s_g[2][KEEP][PT];
   __shared__ uint32_t s_n[2][PT];
+  __shared__ uint64_t s_ok[KEEP][TP];  // thread t's own list: column t
+  __shared__ float s_og[KEEP][TP];
   const int v = blockIdx.y;
   const ViewP& c = P.view[v];
   const uint32_t local = blockIdx.x;
@@ -2697,9 +2716,12 @@ __global__ __launch_bounds__(256) void k_incl_fwd_group(
           fcnt[size_t(b) * TP + tt] = ko;
           kout = ko;
         } else {
-          uint64_t pk[KEEP];
-          float pg[KEEP];
-          uint32_t kp = 0;
+#pragma unroll
+          for (int m = 0; m < KEEP; ++m) {
+            s_ok[m][t] = ok[m];
+            s_og[m][t] = og[m];
+          }
+          uint32_t kp = 0, q = 0;
           if (L == Lt) {  // covering lists of an earlier launch
             const int pi = i >> 1, pj = j >> 1;
             uint32_t pb = 0;
@@ -2711,37 +2733,25 @@ __global__ __launch_bounds__(256) void k_incl_fwd_group(
 #pragma unroll
             for (int m = 0; m < KEEP; ++m) {  // (past kp: slot 0 again, unused)
               const size_t ms = uint32_t(m) < kp ? m : 0;
-              pk[m] = fkey[(size_t(pb) * KEEP + ms) * TP + pt];
-              pg[m] = fgam[(size_t(pb) * KEEP + ms) * TP + pt];
+              s_k[prev][m][t] = fkey[(size_t(pb) * KEEP + ms) * TP + pt];
+              s_g[prev][m][t] = fgam[(size_t(pb) * KEEP + ms) * TP + pt];
             }
+            q = uint32_t(t);
           } else {  // the block of layer L + 1 above, from LDS
-            const int q = ((j >> 1) - ty * (rh >> 1)) * (rw >> 1) + ((i >> 1) - tx * (rw >> 1));
+            q = uint32_t(((j >> 1) - ty * (rh >> 1)) * (rw >> 1) + ((i >> 1) - tx * (rw >> 1)));
             kp = s_n[prev][q];
-#pragma unroll
-            for (int m = 0; m < KEEP; ++m) {
-              pk[m] = s_k[prev][m][q];
-              pg[m] = s_g[prev][m][q];
-            }
           }
           // stable merge of the two sorted lists, own first on equal keys
           uint32_t io = 0, ip = 0, mask = 0;
 #pragma unroll
           for (int m = 0; m < KEEP; ++m) {
-            uint64_t okm = KEY_NONE, pkm = KEY_NONE;
-            float ogm = 0.0f, pgm = 0.0f;
-#pragma unroll
-            for (int r = 0; r < KEEP; ++r) {  // register lists: select slots io and ip
-              okm = uint32_t(r) == io ? ok[r] : okm;
-              ogm = uint32_t(r) == io ? og[r] : ogm;
-              pkm = uint32_t(r) == ip ? pk[r] : pkm;
-              pgm = uint32_t(r) == ip ? pg[r] : pgm;
-            }
-            const uint64_t okv = io < ko ? okm : KEY_NONE;
-            const uint64_t pkv = ip < kp ? pkm : KEY_NONE;
+            const uint32_t jo = min(io, uint32_t(KEEP - 1)), jp = min(ip, uint32_t(KEEP - 1));
+            const uint64_t okv = io < ko ? s_ok[jo][t] : KEY_NONE;
+            const uint64_t pkv = ip < kp ? s_k[prev][jp][q] : KEY_NONE;
             const bool take_o = io < ko && !(pkv < okv);
             const bool take_p = !take_o && ip < kp;
             fk[m] = take_o ? okv : (take_p ? pkv : KEY_NONE);
-            fg[m] = take_o ? ogm : (take_p ? pgm : 0.0f);
+            fg[m] = take_o ? s_og[jo][t] : (take_p ? s_g[prev][jp][q] : 0.0f);
             mask |= (take_p ? 1u : 0u) << m;
             io += take_o ? 1u : 0u;
             ip += take_p ? 1u : 0u;
@@ -4036,21 +4046,28 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
     uint32_t* fcnt = reinterpret_cast<uint32_t*>(sv + lay.s_fcnt);
     // layers 2 and up in groups of up to 1 + log2(shorter tile side) layers counted from
     // layer 2, coarsest group first, each one launch over the tiles of its finest layer;
-    // layers 0 and 1 (most of the texels) keep one launch each
+    // layers 0 and 1 (most of the texels), and a group of one layer, keep one launch each
+    // (a single coarse layer: 4.9 us, by the group kernel 6.6)
     const int gmax = std::min(1 + std::min(P.ltw, 8 - P.ltw), 5);
+    const auto one_layer = [&](int L) {
+      hipLaunchKernelGGL(k_incl_fwd<D>, dim3(layer_quad_grid(P, L), uint32_t(P.V)), dim3(256), 0,
+                         st, P, L, npix, kkey, kgam, fkey, fgam, fcnt, pts.desc, pyr, X.bg,
+                         X.alpha);
+    };
     int L = P.nl - 1;
     while (L >= 2) {
       const int Lb = 2 + ((L - 2) / gmax) * gmax;  // the group's finest layer
-      hipLaunchKernelGGL(k_incl_fwd_group<D>, dim3(layer_tiles_max(P, Lb), uint32_t(P.V)),
-                         dim3(256), 0, st, P, Lb, L, npix, kkey, kgam, fkey, fgam, fcnt,
-                         pts.desc, pyr, X.bg, X.alpha);
+      if (Lb < L)
+        hipLaunchKernelGGL(k_incl_fwd_group<D>, dim3(layer_tiles_max(P, Lb), uint32_t(P.V)),
+                           dim3(256), 0, st, P, Lb, L, npix, kkey, kgam, fkey, fgam, fcnt,
+                           pts.desc, pyr, X.bg, X.alpha);
+      else
+        one_layer(L);
       TRIPS_HIP(hipGetLastError());
       L = Lb - 1;
     }
     for (; L >= 0; --L) {
-      hipLaunchKernelGGL(k_incl_fwd<D>, dim3(layer_quad_grid(P, L), uint32_t(P.V)), dim3(256), 0,
-                         st, P, L, npix, kkey, kgam, fkey, fgam, fcnt, pts.desc, pyr, X.bg,
-                         X.alpha);
+      one_layer(L);
       TRIPS_HIP(hipGetLastError());
     }
   }

@@ -84,3 +84,13 @@ def test_points_with_more_than_four_entries(gpu, n, D):
     import paper_2401_06003_amd as tp
     sc = scenes.random_small(50, n=n, W=96, H=80, nlayers=4, D=D, s_lo=0.5, s_hi=8.0)
     _check(sc, gpu, tp.make_tuning(8, 0, 0))
+
+
+@pytest.mark.parametrize("tile_w,nl,D,n", [(16, 3, 4, 8000), (64, 6, 4, 8000), (8, 7, 8, 8000),
+                                           (16, 8, 4, 3000)])
+def test_inclusion_with_long_own_lists(gpu, tile_w, nl, D, n):
+    """Own lists of up to 16 fragments in the finer layers, merged with full covering lists; layer
+    counts whose coarsest group has one layer, several, or as many as one launch takes."""
+    import paper_2401_06003_amd as tp
+    sc = scenes.random_small(60, n=n, W=61, H=52, nlayers=nl, D=D, s_lo=0.5, s_hi=20.0)
+    _check(sc, gpu, tp.make_tuning(tile_w, 0, 0), include_coarser=True)
