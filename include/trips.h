@@ -92,7 +92,8 @@ typedef struct {
 /* Launch-shape choices (all optional: pass NULL, or 0 in a field, for the defaults).
    tile_w is the width in texels of a screen tile (16x16 by default; tiles always hold
    256 texels: 8x32, 16x16, 32x8, 64x4).  points_per_block is the number of points one
-   binning workgroup histograms (256..65535, default 4096).  item_entries is the number of
+   binning workgroup histograms (256..65535, default 4096, more where many views or tiles
+   would make the tables of counts larger than 256 MB).  item_entries is the number of
    tile entries one sort/blend workgroup consumes before handing over to a merge
    (256..65536; default 8192 for up to one point per pixel of the largest view, doubled for
    each doubling of that density, up to 32768). */

@@ -3678,11 +3678,10 @@ trips_status make_layout(const trips_config* cfg, const trips_camera* cams, int3
   std::memset(&lay, 0, sizeof(lay));
   Params& P = lay.P;
   P.V = views; P.nl = cfg->num_layers; P.D = cfg->desc_dim; P.ltw = ltw; P.eps = cfg->eps;
-  P.pb = uint32_t(pb); P.item_e = uint32_t(item_e); P.n = n;
+  P.item_e = uint32_t(item_e); P.n = n;
   if (cfg->include_coarser != 0 && cfg->include_coarser != 1) return TRIPS_ERR_INVALID_ARG;
   P.coarser = cfg->include_coarser;
   P.fine_e = P.coarser ? 0u : FINE_E;
-  P.nblk = uint32_t((n + pb - 1) / pb);
   const int lth = 8 - ltw;
   uint64_t bins = 0, texels = 0;
   lay.nbv_max = 0;
@@ -3721,6 +3720,23 @@ trips_status make_layout(const trips_config* cfg, const trips_camera* cams, int3
   }
   P.NB = uint32_t(bins);
   lay.npyr = texels;
+  // Points per block by default: 4096, doubled up to 32768 while the tables of counts and their
+  // prefixes (6 bytes per block and tile) are larger than the last-level cache (256 MB) and
+  // halving the blocks leaves 512 of them.  Such tables are written, scanned and read from HBM:
+  // 8M points in 8 views of 2560x1440 have 1.8 GB at 4096 points, and their count, column scan and
+  // scatter take 515, 618 and 2040 us; at 32768 points (230 MB) 430, 107 and 2000 us.  Tables that
+  // the cache holds are better kept at 4096 points (8M points in one view of 1920x1080, 130 MB):
+  // the column scan would take 15 us instead of 48, but the scatter 320 instead of 255.
+  // (The room reserved stays that of the smaller blocks: it must not shrink as n grows.)
+  const size_t room = size_t((n + pb - 1) / pb);
+  if (!tun || !tun->points_per_block) {
+    const auto blocks = [&](int64_t per) { return uint64_t((n + per - 1) / per); };
+    while (pb < 32768 && blocks(pb) * bins * 6 > (256ull << 20) &&
+           blocks(2 * pb) * uint64_t(views) >= 512)
+      pb *= 2;
+  }
+  P.pb = uint32_t(pb);
+  P.nblk = uint32_t((n + pb - 1) / pb);
   lay.ecap = 8ull * uint64_t(n) * uint64_t(views);  // <= 2 layers x 4 tiles per point and view
   if (lay.ecap >= (1ull << 32) - 1) return TRIPS_ERR_CAPACITY;
   lay.icap = bins + (lay.ecap + item_e - 1) / item_e;
@@ -3755,8 +3771,8 @@ trips_status make_layout(const trips_config* cfg, const trips_camera* cams, int3
   o = 0;
   const size_t scratch = o;
   // forward scratch
-  lay.w_H16 = take(size_t(P.nblk) * NB * 2);  // per-block counts per tile
-  lay.w_H = take(size_t(P.nblk) * NB * 4);    // their exclusive prefixes over blocks
+  lay.w_H16 = take(room * NB * 2);  // per-block counts per tile
+  lay.w_H = take(room * NB * 4);    // their exclusive prefixes over blocks
   lay.w_tot = take(NB * 4);
   lay.w_csum = take(((NB + CHUNK - 1) / CHUNK) * CSUM * 4);
   lay.w_coff = take(((NB + CHUNK - 1) / CHUNK) * 4 * 4);

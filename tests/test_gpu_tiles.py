@@ -94,3 +94,36 @@ def test_inclusion_with_long_own_lists(gpu, tile_w, nl, D, n):
     import paper_2401_06003_amd as tp
     sc = scenes.random_small(60, n=n, W=61, H=52, nlayers=nl, D=D, s_lo=0.5, s_hi=20.0)
     _check(sc, gpu, tp.make_tuning(tile_w, 0, 0), include_coarser=True)
+
+
+@pytest.mark.parametrize("n,pb", [(30000, 16384), (40000, 32768), (66000, 65535)])
+def test_large_point_blocks(gpu, n, pb):
+    """Binning workgroups of more than 4096 points, a partly filled last one; tiles with tens of
+    thousands of entries from one block."""
+    import paper_2401_06003_amd as tp
+    sc = scenes.random_small(70, n=n, W=40, H=24, nlayers=3, s_lo=0.3, s_hi=6.0)
+    _check(sc, gpu, tp.make_tuning(16, pb, 0))
+
+
+def test_default_point_blocks_of_large_tables(gpu):
+    """Eight 2560x1440 views of 1.2M points, whose default block is larger than 4096 points: the
+    pyramid and the gradients are those of blocks of 4096."""
+    import torch
+    import paper_2401_06003_amd as tp
+    n, V = 1200000, 8
+    gen = torch.Generator(device=gpu).manual_seed(3)
+    u = lambda lo, hi: lo + (hi - lo) * torch.rand(n, generator=gen, device=gpu)
+    eye = [1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0]
+    cams = [{"R": eye, "t": [0.01 * v, 0.0, 3.0], "fx": 1500.0, "fy": 1500.0, "cx": 1280.0,
+             "cy": 720.0, "W": 2560, "H": 1440, "znear": 0.01} for v in range(V)]
+    args = [u(-1.5, 1.5), u(-1.0, 1.0), u(-0.5, 0.5), u(0.001, 0.01), u(0.1, 1.0),
+            torch.rand(n, 4, generator=gen, device=gpu)]
+    got = []
+    for tuning in (None, tp.make_tuning(0, 4096, 0)):
+        r = tp.Renderer(cams, 6, 4, n, tuning=tuning, device=gpu)
+        out = r.forward(*args).clone()
+        G = torch.linspace(-1.0, 1.0, out.numel(), device=gpu)
+        got.append([out] + [g.clone() for g in r.backward(*args, G)])
+        del r
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
