@@ -74,8 +74,7 @@ def method_bytes(stage, w):
         "fwd_items": 8 * Fc + 4 * Kc + 4 * D * Pc + 4 * D * Nv * share_c,
         "fwd_fine": 8 * Ff + 4 * Kf + 4 * D * Pf + 4 * D * Nv * share_f,
         "fwd_merge": 0,
-        "bwd_pixels": 4 * Kc + 4 * D * Pc + 4 * D * Nv * share_c,
-        "bwd_items": 0,
+        "bwd_items": 4 * Kc + 4 * D * Pc + 4 * D * Nv * share_c,
         "bwd_fine": 4 * Kf + 4 * D * Pf + 4 * D * Nv * share_f,
         "bwd_points": 20 * Nv + 4 * (5 + D) * N,
     }
@@ -84,23 +83,24 @@ def method_bytes(stage, w):
 
 def impl_bytes(stage, w):
     """The implementation's own byte model of one launch (reads + writes of its data
-    structures: 20-byte tile entries, 32-byte rows, 16-bit per-block histograms and their
-    32-bit prefixes, kept keys and gammas), for comparison with the method's bytes and the
-    counters."""
+    structures: 20-byte tile entries, 32-byte rows (in the tiles of work items only of entries
+    that keep a fragment, at most one per kept fragment), a bit per entry that says so, 16-bit
+    per-block histograms and their 32-bit prefixes, kept keys and gammas), for comparison with
+    the method's bytes and the counters."""
     N, D, E, Ef, K, Kf, Nv = w["N"], w["D"], w["E"], w["E_f"], w["K"], w["K_f"], w["Nv"]
     NB, NBf, Ic, Pc, Pf, nblk = w["NB"], w["NB_f"], w["I_c"], w["P_c"], w["P_f"], w["nblk"]
     Ec, Kc, NBc = E - Ef, K - Kf, NB - NBf
     row = 4 * (4 + D)
+    Rc = min(Ec, Kc)
     table = {
         "count": 16 * N + 2 * nblk * NB,
         "colscan": 6 * nblk * NB + 4 * NB,
-        "scatter": 20 * N + 4 * nblk * NB + 4 * NB + 20 * E + 32 * Nv,
+        "scatter": 20 * N + 4 * nblk * NB + 4 * NB + 20 * E + 16 * Nv + E / 8,
         "fwd_items": 20 * Ec + (4 * D + 12) * Kc + 4 * 256 * NBc + 4 * D * Pc,
         "fwd_fine": (24 + 4 * D) * Ef + 12 * Kf + 4 * 256 * NBf + 4 * D * Pf,
-        "bwd_pixels": 4 * 256 * NBc + (12 + 4 * D + 8) * Kc + 4 * D * Pc,
-        "bwd_items": (20 + row) * Ec + 16 * Kc + Ic * 256 * (4 + 4 * D),
+        "bwd_items": 20 * Ec + Ec / 8 + row * Rc + (12 + 4 * D) * Kc + Ic * 256 * (4 + 4 * D),
         "bwd_fine": (24 + 4 * D + row) * Ef + 4 * 256 * NBf + 4 * D * Pf,
-        "bwd_points": 20 * N + 32 * Nv + row * E + 4 * (5 + D) * N,
+        "bwd_points": 20 * N + 16 * Nv + E / 8 + row * (Rc + Ef) + 4 * (5 + D) * N,
     }
     return table.get(stage)
 
@@ -779,7 +779,7 @@ def main():
     achieved = dom_bytes / (stage_ms[dom] / 1e3) / 1e9
     sbytes = step_bytes(N, w["Nv"], D, w["F"], w["K"], w["P"])
     assert abs(sum(method_bytes(k, w) for k in
-                   ("count", "scatter", "fwd_items", "fwd_fine", "bwd_pixels", "bwd_fine",
+                   ("count", "scatter", "fwd_items", "fwd_fine", "bwd_items", "bwd_fine",
                     "bwd_points")) - sbytes) <= 1e-6 * sbytes
     step_meas = measured_traffic(dom, "step_bytes")
     out = {

@@ -17,9 +17,9 @@
  *    TRIPS_ERR_HIP and the HIP error code is kept for trips_last_hip_error().
  *  - All work is enqueued on `stream` in order; results are ready when the stream is.
  *    Part of a forward or backward call (the kernels of the tiles with few entries), except
- *    in uncaptured calls of a few thousand points, runs on a second stream of the device that the library creates once, with the default
- *    priority, forked from `stream` and joined back into it within the call; captured into
- *    a graph, the two become branches of it.
+ *    in uncaptured calls of a few thousand points, runs on a second stream of the device that
+ *    the library creates once, with the default priority, forked from `stream` and joined
+ *    back into it within the call; captured into a graph, the two become branches of it.
  *  - Up to TRIPS_MAX_VIEWS views of arbitrary, different resolutions are rendered by
  *    one call ("batched views"); every point is read once per call and projected
  *    into every view.  Gradients are summed over the views of a call.

@@ -13,13 +13,19 @@
 //   colscan    per bin, exclusive prefix of H16 over blocks (32-bit, into H) and bin totals.
 //   binscan    exclusive scans of bin totals -> bin starts, and of work items -> item starts.
 //   scatter    same blocks again: LDS ranks, entry written at bin_start + H + rank.
-//   fwd_items  persistent: one workgroup per work item (a bin, or a chunk of a heavy bin);
+//   front      count to scatter in one workgroup, for one view of at most 4096 points.
+//   fwd_items  one workgroup per work item (a bin, or a chunk of a heavy bin);
 //              entries -> fragments in LDS, counting sort by texel, per-texel top-16 kept
 //              in registers (thread = texel); blend, or write a partial top-16.
+//   fwd_select the same for calls of fewer points: the top 16 of a texel selected by counting
+//              its fragments in depth bins.
+//   fwd_fine   one workgroup per bin of at most 256 entries, sorted in LDS; beside fwd_items.
 //   fwd_merge  heavy bins: merge the partial top-16 lists, blend.
+//   incl_fwd   (with coarser-layer inclusion) merge every texel's list with its covering one's.
 //   bwd_items  per work item: recompute T_m per texel, reverse recurrence -> (dgamma_m,
 //              T_m gamma_m) in LDS; every entry looks its corners up in the tile's kept
 //              lists and, if one is kept, writes one partial-gradient row.
+//   bwd_fine   the same for the bins of fwd_fine, beside bwd_items.
 //   bwd_points per point: sum its rows, chain rule through the projection, write grads.
 // Every result is deterministic: ordering keys are unique (depth bits, point index) and
 // every sum is taken in a fixed order.
