@@ -2111,8 +2111,12 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
   // the tile's kept depths and, without inclusion, its blend adjoints
   {
     const int x = t & (TP - 1), h = t / TP;
-    const uint32_t n = npix[size_t(b) * TP + x];
-    const uint32_t k = INC ? (fcnt[size_t(b) * TP + x] & 31u) : min(n, uint32_t(KEEP));
+    const int i = tg.x0 + (x & ((1 << P.ltw) - 1)), j = tg.y0 + (x >> P.ltw);
+    const bool in = i < bi.WL && j < bi.HL;  // (texels with fragments are)
+    // (the inclusion passes write no count for a texel outside the layer: its word is whatever the
+    // buffer held, and must not become a list length)
+    const uint32_t n = INC ? fcnt[size_t(b) * TP + x] & 31u : npix[size_t(b) * TP + x];
+    const uint32_t k = in ? min(n, uint32_t(KEEP)) : 0u;
     uint64_t raw[LQ];
     float gam[LQ];
     // all loads are issued together: slots past the list read slot 0 of the same texel (a valid
@@ -2123,8 +2127,6 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
       raw[q] = kkey[o];
       if (!INC) gam[q] = kgam[o];
     }
-    const int i = tg.x0 + (x & ((1 << P.ltw) - 1)), j = tg.y0 + (x >> P.ltw);
-    const bool in = i < bi.WL && j < bi.HL;  // (texels with fragments are)
     // (of a tile cut into items, the item with the tile's first entry writes the background)
     const bool first_part = !(wk.w >> 31) || e0 == bin_start[b];
     const size_t tex = size_t(P.view[bi.v].lout[bi.L]) + size_t(in ? j : 0) * bi.WL + (in ? i : 0);
