@@ -739,7 +739,6 @@ __global__ __launch_bounds__(BIN_THREADS) void k_scatter(const Params P, const f
                                                          const uint32_t* __restrict__ bin_start,
                                                          Entry* __restrict__ ent,
                                                          uint32_t* __restrict__ epos,
-                                                         uint64_t* __restrict__ kept,
                                                          uint32_t* __restrict__ info) {
   extern __shared__ uint32_t lds[];
   __shared__ uint32_t s_vis;
@@ -753,8 +752,6 @@ __global__ __launch_bounds__(BIN_THREADS) void k_scatter(const Params P, const f
   const uint32_t* bs = bin_start + c.bin_base;
   if (threadIdx.x == 0) s_vis = 0;
   for (uint32_t i = threadIdx.x; i < nw; i += blockDim.x) hist[i] = 0;
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i <= info[0] / 64; i += gridDim.x * blockDim.x)
-    kept[i] = 0;  // for the backward (mark_kept)
   if (STAGED) {  // SB bins per thread in flight (a 1080p view's tiles in one batch)
     constexpr int SB = 12;
     for (uint32_t i0 = threadIdx.x; i0 < c.nbins; i0 += SB * blockDim.x) {
@@ -835,8 +832,7 @@ __global__ __launch_bounds__(FRONT_T) void k_front(
     const float* __restrict__ Z, const float* __restrict__ SW, const float* __restrict__ A,
     uint32_t* __restrict__ bin_start, uint32_t* __restrict__ item_start,
     uint32_t* __restrict__ multi_bins, uint4* __restrict__ fine_work, uint32_t* __restrict__ info,
-    uint4* __restrict__ work, Entry* __restrict__ ent, uint32_t* __restrict__ epos,
-    uint64_t* __restrict__ kept) {
+    uint4* __restrict__ work, Entry* __restrict__ ent, uint32_t* __restrict__ epos) {
   extern __shared__ uint32_t lds[];
   __shared__ uint4 s_scan[FRONT_T / 64];
   __shared__ uint32_t s_cls[NBUCKET], s_base[NBUCKET], s_vis;
@@ -921,7 +917,6 @@ __global__ __launch_bounds__(FRONT_T) void k_front(
     }
     o.x += k.e; o.y += k.it; o.z += k.multi; o.w += k.fine;
   }
-  for (uint32_t i = t; i <= all.x / 64; i += FRONT_T) kept[i] = 0;
   __syncthreads();
   uint32_t vis = 0;
 #pragma unroll
@@ -1004,17 +999,6 @@ __device__ __forceinline__ int tile_corners(const TileGeo& g, float u, float v, 
   const bool ya = (uint32_t(lj) <= g.ym) & (fv != 1.0f), yb = (uint32_t(lj + 1) <= g.ym) & (fv != 0.0f);
   const int m = int(xa & ya) | (int(xb & ya) << 1) | (int(xa & yb) << 2) | (int(xb & yb) << 3);
   return int(uint32_t((lj << g.ltw) + li) << 4) | m;
-}
-
-// Which entries kept a fragment, one bit each (entry e: bit e % 64 of word e / 64), so that the
-// rows of the others need neither be written nor read.  The forward clears the words; a
-// wavefront whose lanes hold consecutive entries from e on ORs its ballot into the two words
-// it covers (tiles start anywhere in a word).
-__device__ __forceinline__ void mark_kept(unsigned long long* kept, uint32_t e, uint64_t ballot) {
-  const uint32_t s = e & 63u;
-  const uint64_t lo = ballot << s, hi = s ? ballot >> (64u - s) : 0ull;
-  if (lo) atomicOr(&kept[e >> 6], lo);
-  if (hi) atomicOr(&kept[(e >> 6) + 1], hi);
 }
 
 // Optional inputs and outputs around the blend (any may be null): a background composited
@@ -2054,7 +2038,9 @@ __device__ __forceinline__ float2 blend_adjoint_step(float Tm, float gam, float 
 // entries that have such a corner until every lane holds one.  The lists are in depth order, so a
 // kept corner's slot is found by bisection of the texel's depths in LDS (four reads instead of a
 // comparison with all 16 point ids); where a list holds equal depths the stored keys tell.  An
-// entry without a kept corner writes no row, only its bit in `kept`.
+// entry without a kept corner writes no row, only its mark in `kept`: a byte per entry, written
+// here or by bwd_fine for every entry of the call, so nothing is cleared first and `saved` stays
+// as the forward left it.
 // With coarser-layer inclusion (INC) the kept own fragments are those the blended list took
 // (a prefix of the own list), and each one's totals (dL/dgamma, tau part) are read from
 // itot instead of being formed from the blend adjoint and G.
@@ -2071,7 +2057,7 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
     const uint32_t* __restrict__ npix, const uint64_t* __restrict__ kkey,
     const float* __restrict__ kgam, const float* __restrict__ desc,
     const float* __restrict__ gpyr, float* __restrict__ rows,
-    unsigned long long* __restrict__ kept, const uint32_t* __restrict__ fcnt,
+    uint8_t* __restrict__ kept, const uint32_t* __restrict__ fcnt,
     const float* __restrict__ itot, const Extras X) {
   constexpr int RW = 4 + D;
   constexpr int S = D + 1;
@@ -2294,9 +2280,9 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
         pm |= int(on) << q;
       }
       const bool any = (pm & 15) != 0;
+      if (eh < e1) kept[eh] = any ? 1 : 0;
       const uint64_t bits = __ballot(any);
       if (bits == 0) continue;  // (uniform)
-      if (lane == 0) mark_kept(kept, eh, bits);
       // the entries with kept corners move to the lanes from `waiting` on, the others behind them
       const uint32_t nk = uint32_t(__popcll(bits));
       const uint32_t before = __builtin_amdgcn_mbcnt_hi(uint32_t(bits >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bits), 0u));
@@ -2332,7 +2318,7 @@ __global__ __launch_bounds__(256) void k_bwd_fine(
     const Params P, const uint32_t* __restrict__ info, const uint4* __restrict__ fine_work,
     const Entry* __restrict__ ent, const uint32_t* __restrict__ kslot,
     const uint32_t* __restrict__ npix, const float* __restrict__ desc,
-    const float* __restrict__ gpyr, float* __restrict__ rows, unsigned long long* __restrict__ kept,
+    const float* __restrict__ gpyr, float* __restrict__ rows, uint8_t* __restrict__ kept,
     const Extras X) {
   constexpr int RW = 4 + D;
   constexpr int NF = 4 * FINE_E;  // at most one kept fragment per fragment
@@ -2431,10 +2417,7 @@ __global__ __launch_bounds__(256) void k_bwd_fine(
     }
     if (X.gbg) write_scaled<D>(X.gbg + tex * D, T, G);
   }
-  {  // which entries kept a fragment; the others write no row
-    const uint64_t bits = __ballot(cm != 0);
-    if ((t & 63) == 0) mark_kept(kept, e0 + t, bits);
-  }
+  if (has) kept[e0 + t] = cm != 0 ? 1 : 0;  // (an entry that kept no fragment writes no row)
   __syncthreads();
   if (cm == 0) return;
   float2 st[4];
@@ -3405,14 +3388,16 @@ __global__ __launch_bounds__(256) void k_incl_bwd012(
 // d/dR (row-major, X_c = R X_w + t), d/dt, d/dfx, d/dfy, d/dcx, d/dcy, written to
 // campart[block][view][16] for k_cam_reduce.
 // Bound by memory: the entry positions, the rows (a 128-byte line for 32 bytes) and the
-// gradients.  The kept bits (a bit per entry: they stay in the L2) keep it from fetching the rows
-// of entries without a kept fragment: 2.04 -> 1.78 ms on eight 2560x1440 views, 250 -> 231 us at
-// 8M points (1920x1080), 67 us as before at 2M.
+// gradients.  The kept marks keep it from fetching the rows of entries without a kept fragment:
+// 2.04 -> 1.78 ms on eight 2560x1440 views, 250 -> 231 us at 8M points (1920x1080), 67 us as before
+// at 2M.  (Measured with a bit per entry; a byte, which needs no clearing and no atomics, is the
+// same within the noise: forward + backward 1.286 and 1.293 ms at 8M points, 12.03 and 12.00 ms on
+// the eight views.)
 template <int D, bool CAM>
 __global__ __launch_bounds__(256) void k_bwd_points(
     const Params P, const float* __restrict__ X, const float* __restrict__ Y,
     const float* __restrict__ Z, const float* __restrict__ SW, const float* __restrict__ A,
-    const float* __restrict__ rows, const uint32_t* __restrict__ kept, float* __restrict__ gX, float* __restrict__ gY,
+    const float* __restrict__ rows, const uint8_t* __restrict__ kept, float* __restrict__ gX, float* __restrict__ gY,
     float* __restrict__ gZ, float* __restrict__ gSW, float* __restrict__ gA,
     float* __restrict__ gD, const uint32_t* __restrict__ epos, float* __restrict__ campart) {
   constexpr int RW = 4 + D;
@@ -3448,7 +3433,7 @@ __global__ __launch_bounds__(256) void k_bwd_points(
 #pragma unroll
       for (int d = 0; d < D; ++d) gt[d] = 0.0f;
       // both layer entries' footprints and the point's entry positions, then the entries' kept
-      // bits, then all eight rows at once: a slot without a kept entry reads row 0 and is
+      // marks, then all eight rows at once: a slot without a kept entry reads row 0 and is
       // dropped, so no load waits on another of its kind
       uint32_t tm[2][4];
       const uint32_t last = uint32_t(8 * P.n * P.V) - 1u;  // row capacity (guards memory only)
@@ -3479,10 +3464,10 @@ __global__ __launch_bounds__(256) void k_bwd_points(
         }
       }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) kb[k] = kept[(tm[k >> 2][k & 3] ? min(er[k], last) : 0u) >> 5];
+      for (int k = 0; k < 8; ++k) kb[k] = kept[tm[k >> 2][k & 3] ? min(er[k], last) : 0u];
 #pragma unroll
       for (int k = 0; k < 8; ++k)
-        if (!((kb[k] >> (er[k] & 31u)) & 1u)) tm[k >> 2][k & 3] = 0;
+        if (!kb[k]) tm[k >> 2][k & 3] = 0;
       float4 rv[2][4][1 + D / 4];
 #pragma unroll
       for (int sel = 0; sel < 2; ++sel)
@@ -3643,11 +3628,11 @@ struct Layout {
   uint64_t npyr;      // texels of all views and layers
   // saved buffer
   size_t s_info, s_bin_start, s_item_start, s_multi, s_fine, s_npix, s_kkey, s_kgam,
-      s_fkey, s_fgam, s_fcnt, s_kslot, s_tables_end, s_work, s_ent, s_epos, s_kept;
+      s_fkey, s_fgam, s_fcnt, s_kslot, s_tables_end, s_work, s_ent, s_epos;
   size_t saved_bytes;
   // workspace
-  size_t w_H16, w_H, w_tot, w_csum, w_coff, w_pcnt, w_pkey, w_pgam, w_rows, w_cam, w_itot, w_iup,
-      ws_bytes;
+  size_t w_H16, w_H, w_tot, w_csum, w_coff, w_pcnt, w_pkey, w_pgam, w_rows, w_kept, w_cam, w_itot,
+      w_iup, ws_bytes;
   size_t ws_fwd_bytes;  // the part of the workspace a forward call uses
 };
 
@@ -3779,7 +3764,6 @@ trips_status make_layout(const trips_config* cfg, const trips_camera* cams, int3
   lay.s_work = take(size_t(lay.icap) * sizeof(uint4));
   lay.s_ent = take(size_t(lay.ecap) * sizeof(Entry));
   lay.s_epos = take(size_t(views) * NSLOT * size_t(n) * 4);
-  lay.s_kept = take((size_t(lay.ecap) / 64 + 2) * 8);  // a bit per entry: has a kept fragment
   lay.saved_bytes = o;
   o = 0;
   const size_t scratch = o;
@@ -3799,6 +3783,7 @@ trips_status make_layout(const trips_config* cfg, const trips_camera* cams, int3
   // backward scratch reuses the same bytes
   o = scratch;
   lay.w_rows = take(size_t(views) * NSLOT * size_t(n) * (4 + P.D) * 4);
+  lay.w_kept = take(size_t(lay.ecap));  // a byte per entry: has a kept fragment
   lay.w_cam = take(size_t((n + 255) / 256) * size_t(views) * 16 * 4);
   lay.w_itot = take(inc * NB * TP * KEEP * size_t(1 + P.D) * 4);
   lay.w_iup = take(inc * NB * TP * KEEP * size_t(1 + P.D) * 4);
@@ -3983,14 +3968,13 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
   Entry* ent = reinterpret_cast<Entry*>(sv + lay.s_ent);
   uint32_t* epos = reinterpret_cast<uint32_t*>(sv + lay.s_epos);
   uint32_t* kslot = reinterpret_cast<uint32_t*>(sv + lay.s_kslot);
-  uint64_t* kept = reinterpret_cast<uint64_t*>(sv + lay.s_kept);
 
   // few points in a single view are binned by one workgroup, if its tables fit in LDS
   if (P.n > 0 && P.n <= int64_t(FRONT_N) && P.V == 1 && staged_scatter_lds(lay.nbv_max) <= kLdsLimit) {
     StageTimer tm(ST_SCATTER, st);
     hipLaunchKernelGGL(k_front, dim3(1), dim3(FRONT_T), staged_scatter_lds(lay.nbv_max), st, P,
                        pts.x, pts.y, pts.z, pts.size_w, pts.opacity, bin_start, item_start,
-                       multi_bins, fine_work, info, work, ent, epos, kept);
+                       multi_bins, fine_work, info, work, ent, epos);
     TRIPS_HIP(hipGetLastError());
   } else {
     if (P.nblk > 0) {
@@ -4031,11 +4015,11 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
       if (staged_scatter_lds(lay.nbv_max) <= kLdsLimit)
         hipLaunchKernelGGL(k_scatter<true>, dim3(P.nblk * P.V), dim3(BIN_THREADS),
                            staged_scatter_lds(lay.nbv_max), st, P, pts.x, pts.y, pts.z, pts.size_w,
-                           pts.opacity, H, bin_start, ent, epos, kept, info);
+                           pts.opacity, H, bin_start, ent, epos, info);
       else
         hipLaunchKernelGGL(k_scatter<false>, dim3(P.nblk * P.V), dim3(BIN_THREADS),
                            count_lds(lay.nbv_max), st, P, pts.x, pts.y, pts.z, pts.size_w,
-                           pts.opacity, H, bin_start, ent, epos, kept, info);
+                           pts.opacity, H, bin_start, ent, epos, info);
     }
     TRIPS_HIP(hipGetLastError());
   }
@@ -4105,11 +4089,11 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
 
 template <int D>
 trips_status launch_backward(const Layout& lay, const trips_points& pts, const float* gpyr,
-                             char* sv, char* ws, float* gx, float* gy, float* gz, float* gsw,
+                             const char* sv, char* ws, float* gx, float* gy, float* gz, float* gsw,
                              float* ga, float* gd, const Extras& X, hipStream_t st) {
   const Params& P = lay.P;
   float* rows = reinterpret_cast<float*>(ws + lay.w_rows);
-  unsigned long long* kept = reinterpret_cast<unsigned long long*>(sv + lay.s_kept);
+  uint8_t* kept = reinterpret_cast<uint8_t*>(ws + lay.w_kept);
   const uint32_t* bin_start = reinterpret_cast<const uint32_t*>(sv + lay.s_bin_start);
   const uint32_t* item_start = reinterpret_cast<const uint32_t*>(sv + lay.s_item_start);
   const uint32_t* info = reinterpret_cast<const uint32_t*>(sv + lay.s_info);
@@ -4192,13 +4176,11 @@ trips_status launch_backward(const Layout& lay, const trips_points& pts, const f
     float* campart = reinterpret_cast<float*>(ws + lay.w_cam);
     if (X.gcam)
       hipLaunchKernelGGL((k_bwd_points<D, true>), dim3(grid), dim3(256), 0, st, P, pts.x, pts.y,
-                         pts.z, pts.size_w, pts.opacity, rows,
-                         reinterpret_cast<const uint32_t*>(kept), gx, gy, gz, gsw, ga, gd, epos,
+                         pts.z, pts.size_w, pts.opacity, rows, kept, gx, gy, gz, gsw, ga, gd, epos,
                          campart);
     else
       hipLaunchKernelGGL((k_bwd_points<D, false>), dim3(grid), dim3(256), 0, st, P, pts.x, pts.y,
-                         pts.z, pts.size_w, pts.opacity, rows,
-                         reinterpret_cast<const uint32_t*>(kept), gx, gy, gz, gsw, ga, gd, epos,
+                         pts.z, pts.size_w, pts.opacity, rows, kept, gx, gy, gz, gsw, ga, gd, epos,
                          campart);
   }
   TRIPS_HIP(hipGetLastError());
@@ -4367,8 +4349,7 @@ trips_status trips_backward(const trips_config* cfg, const trips_points* pts,
     return TRIPS_ERR_INVALID_ARG;
   Extras X;
   if ((s = take_extras(extras, false, true, X)) != TRIPS_OK) return s;
-  // of `saved` the backward writes the kept bits only (the same ones whatever the gradients)
-  char* sv = const_cast<char*>(static_cast<const char*>(saved));
+  const char* sv = static_cast<const char*>(saved);
   char* w = static_cast<char*>(ws);
   return cfg->desc_dim == 4 ? launch_backward<4>(lay, *pts, gpyr, sv, w, gx, gy, gz, gsw, ga, gd, X, st)
                             : launch_backward<8>(lay, *pts, gpyr, sv, w, gx, gy, gz, gsw, ga, gd, X, st);

@@ -33,3 +33,24 @@ def test_inclusion_ignores_what_the_buffers_held(gpu, W, H, nl, D, tile_w):
         for a, b in zip(got[0], other):
             assert torch.equal(a, b)
     assert all(float(np.abs(g.numpy()).max()) > 0 for g in got[0][1:])
+
+
+@pytest.mark.parametrize("n,D,coarser", [(300, 4, False), (9000, 8, False), (5000, 4, True)])
+def test_backward_leaves_saved_as_it_was(gpu, n, D, coarser):
+    """`saved` is const to the backward: not a byte of it changes, and a second backward from it,
+    into a workspace that held something else, gives the same gradients."""
+    import torch
+    sc = scenes.random_small(85, n=n, W=90, H=61, nlayers=5, D=D, s_lo=0.4, s_hi=12.0)
+    r = renderer(sc, gpu, include_coarser=coarser)
+    t = to_device(sc["points"], gpu)
+    args = [t[k] for k in PARAMS]
+    r.saved.zero_()
+    r.forward(*args)
+    before = r.saved.clone()
+    G = torch.from_numpy(scenes.upstream_gradient(86, r.texels * D)).to(gpu)
+    first = r.backward(*args, G)
+    assert torch.equal(r.saved, before)
+    r.workspace.fill_(0xff)
+    for a, b in zip(first, r.backward(*args, G)):
+        assert torch.equal(a, b)
+    assert torch.equal(r.saved, before)
