@@ -3578,11 +3578,11 @@ thread_local int32_t g_last_hip = 0;
 // Optional per-kernel timing (reports only): a start and an end event around every kernel
 // launch, on the launch stream; read back and summed per stage by trips_timing_read.
 enum Stage { ST_COUNT, ST_COLSCAN, ST_BINSCAN, ST_SCATTER, ST_FWD_ITEMS,
-             ST_FWD_FINE, ST_FWD_MERGE, ST_BWD_PIXELS, ST_BWD_ITEMS, ST_BWD_FINE, ST_BWD_POINTS,
+             ST_FWD_FINE, ST_FWD_MERGE, ST_FRONT, ST_BWD_ITEMS, ST_BWD_FINE, ST_BWD_POINTS,
              ST_EXPORT, ST_INCL_FWD, ST_INCL_BWD, NUM_STAGES };
 const char* const kStageNames[NUM_STAGES] = {
     "count", "colscan", "binscan", "scatter", "fwd_items", "fwd_fine", "fwd_merge",
-    "bwd_pixels", "bwd_items", "bwd_fine", "bwd_points", "export", "incl_fwd", "incl_bwd"};
+    "front", "bwd_items", "bwd_fine", "bwd_points", "export", "incl_fwd", "incl_bwd"};
 static_assert(NUM_STAGES == TRIPS_NUM_STAGES, "stage table");
 
 struct TimingState {
@@ -3971,7 +3971,7 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
 
   // few points in a single view are binned by one workgroup, if its tables fit in LDS
   if (P.n > 0 && P.n <= int64_t(FRONT_N) && P.V == 1 && staged_scatter_lds(lay.nbv_max) <= kLdsLimit) {
-    StageTimer tm(ST_SCATTER, st);
+    StageTimer tm(ST_FRONT, st);
     hipLaunchKernelGGL(k_front, dim3(1), dim3(FRONT_T), staged_scatter_lds(lay.nbv_max), st, P,
                        pts.x, pts.y, pts.z, pts.size_w, pts.opacity, bin_start, item_start,
                        multi_bins, fine_work, info, work, ent, epos);
