@@ -38,7 +38,6 @@
 #include <cstring>
 #include <mutex>
 #include <new>
-#include <type_traits>
 #include <vector>
 
 #include "trips.h"
@@ -4095,7 +4094,6 @@ trips_status launch_backward(const Layout& lay, const trips_points& pts, const f
   float* rows = reinterpret_cast<float*>(ws + lay.w_rows);
   uint8_t* kept = reinterpret_cast<uint8_t*>(ws + lay.w_kept);
   const uint32_t* bin_start = reinterpret_cast<const uint32_t*>(sv + lay.s_bin_start);
-  const uint32_t* item_start = reinterpret_cast<const uint32_t*>(sv + lay.s_item_start);
   const uint32_t* info = reinterpret_cast<const uint32_t*>(sv + lay.s_info);
   const uint4* work = reinterpret_cast<const uint4*>(sv + lay.s_work);
   const uint4* fine_work = reinterpret_cast<const uint4*>(sv + lay.s_fine);
