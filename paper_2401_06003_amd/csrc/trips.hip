@@ -819,13 +819,18 @@ __global__ __launch_bounds__(BIN_THREADS) void k_scatter(const Params P, const f
 // workgroup: its histogram is the tile totals, so no matrix and no scan over blocks is needed,
 // and the tables of count, binscan and scatter come out the same.  For so few points the four
 // launches are latency and one busy CU each; here every thread projects its points once and
-// keeps their entries (tile, place in the tile, footprint) in registers until the tiles'
-// starts are known.
+// keeps their entries (tile, place in the tile, footprint) until the tiles' starts are known, in
+// registers except for 38 words of a thread that are spilled (128 registers are all a workgroup of
+// 1024 threads has).
 // Bound by one CU's instruction issue: 4096 points, 256x256: 29 us, for 43 us of the four
 // kernels and three gaps; 300 points 12 us.
 constexpr uint32_t FRONT_T = 1024;
 constexpr int FRONT_P = 4;  // points per thread
 constexpr uint32_t FRONT_N = FRONT_T * FRONT_P;
+// ... and it goes through the view's tiles alone: up to this many.  Forward of 64 points at
+// 1920x1080 (10,902 tiles) 49 us, by the four kernels 65; 2560x1440 (19,243) 75 and 76; 2880x1620
+// (24,535) 91 and 82, of 4096 points 114 and 107.
+constexpr uint32_t FRONT_BINS = 20 * FRONT_T;
 __global__ __launch_bounds__(FRONT_T) void k_front(
     const Params P, const float* __restrict__ X, const float* __restrict__ Y,
     const float* __restrict__ Z, const float* __restrict__ SW, const float* __restrict__ A,
@@ -3968,8 +3973,9 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
   uint32_t* epos = reinterpret_cast<uint32_t*>(sv + lay.s_epos);
   uint32_t* kslot = reinterpret_cast<uint32_t*>(sv + lay.s_kslot);
 
-  // few points in a single view are binned by one workgroup, if its tables fit in LDS
-  if (P.n > 0 && P.n <= int64_t(FRONT_N) && P.V == 1 && staged_scatter_lds(lay.nbv_max) <= kLdsLimit) {
+  // few points in a single view of not too many tiles are binned by one workgroup
+  static_assert(size_t(FRONT_BINS) * 6 <= kLdsLimit, "the tables of the tiles fit");
+  if (P.n > 0 && P.n <= int64_t(FRONT_N) && P.V == 1 && P.NB <= FRONT_BINS) {
     StageTimer tm(ST_FRONT, st);
     hipLaunchKernelGGL(k_front, dim3(1), dim3(FRONT_T), staged_scatter_lds(lay.nbv_max), st, P,
                        pts.x, pts.y, pts.z, pts.size_w, pts.opacity, bin_start, item_start,
