@@ -827,10 +827,11 @@ __global__ __launch_bounds__(BIN_THREADS) void k_scatter(const Params P, const f
 constexpr uint32_t FRONT_T = 1024;
 constexpr int FRONT_P = 4;  // points per thread
 constexpr uint32_t FRONT_N = FRONT_T * FRONT_P;
-// ... and it goes through the view's tiles alone: up to this many.  Forward of 64 points at
-// 1920x1080 (10,902 tiles) 49 us, by the four kernels 65; 2560x1440 (19,243) 75 and 76; 2880x1620
-// (24,535) 91 and 82, of 4096 points 114 and 107.
-constexpr uint32_t FRONT_BINS = 20 * FRONT_T;
+// ... and it goes through the view's tiles alone: up to this many.  Forward of 64 and 4096 points
+// by it and by the four kernels: 1280x720 (4,843 tiles) 30 and 52 us against 39 and 63, 1920x1080
+// (10,902) 48 and 70 against 49 and 73, 2048x1152 (12,297) 53 and 75 against 51 and 75, 2560x1440
+// (19,243) 74 and 96 against 66 and 89.
+constexpr uint32_t FRONT_BINS = 11 * FRONT_T;
 __global__ __launch_bounds__(FRONT_T) void k_front(
     const Params P, const float* __restrict__ X, const float* __restrict__ Y,
     const float* __restrict__ Z, const float* __restrict__ SW, const float* __restrict__ A,

@@ -48,28 +48,28 @@ def test_every_stage_is_some_kernel(gpu):
 
 
 @pytest.mark.parametrize("n", [1, 700, 4096])
-def test_one_workgroup_binning_up_to_20480_tiles(gpu, n):
-    """A view of 20,400 tiles is binned by one workgroup, one of 20,500 by the four passes; the
-    second is the first with five more columns of tiles to the right of every point, so the common
+def test_one_workgroup_binning_up_to_11264_tiles(gpu, n):
+    """A view of 11,200 tiles is binned by one workgroup, one of 11,300 by the four passes; the
+    second is the first with one more column of tiles to the right of every point, so the common
     texels and the gradients are the same, bit for bit."""
     import torch
-    sc = scenes.random_small(110 + n, n=n, W=3264, H=1600, nlayers=1, s_lo=0.3, s_hi=3.0)
+    sc = scenes.random_small(110 + n, n=n, W=1792, H=1600, nlayers=1, s_lo=0.3, s_hi=3.0)
     t = to_device(sc["points"], gpu)
     args = [t[k] for k in PARAMS]
     cam = dict(sc["cams"][0])
     px = args[0] / args[2] * float(cam["fx"]) + float(cam["cx"])
-    args[0] = torch.where(px < 3200.0, args[0], -args[0]).contiguous()
-    G = torch.from_numpy(scenes.upstream_gradient(111, 3280 * 1600 * 4)).to(gpu).view(1600, 3280, 4)
+    args[0] = torch.where(px < 1780.0, args[0], -args[0]).contiguous()
+    G = torch.from_numpy(scenes.upstream_gradient(111, 1808 * 1600 * 4)).to(gpu).view(1600, 1808, 4)
     got = []
-    for W in (3264, 3280):
+    for W in (1792, 1808):
         r = renderer(sc, gpu, cams=[dict(cam, W=W)])
         res = []
         lt = _launches(lambda: res.append(r.forward(*args)))
         assert r.stats()["bins"] == W // 16 * 100
-        assert (lt["front"], lt["count"]) == ((1, 0) if W == 3264 else (0, 1))
+        assert (lt["front"], lt["count"]) == ((1, 0) if W == 1792 else (0, 1))
         assert r.stats()["visible"] > 0
         g = r.backward(*args, G[:, :W].contiguous().view(-1))
-        got.append([res[0].view(1600, W, 4)[:, :3264]] + g)
+        got.append([res[0].view(1600, W, 4)[:, :1792]] + g)
     for a, b in zip(*got):
         assert torch.equal(a, b)
     assert float(got[0][0].abs().max()) > 0
