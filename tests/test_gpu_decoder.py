@@ -170,3 +170,50 @@ def test_rendered_pyramid_decodes(gpu):
         o += w * h
     ref, _ = dec.decode(layers, wt, fp16=True)
     _net_check(img, ref)
+
+
+@pytest.mark.parametrize("D,below,out_dim", [(4, True, 5), (8, True, 3), (8, True, 5), (4, False, 3),
+                                             (8, False, 8)])
+def test_layer_of_many_tiles(gpu, D, below, out_dim):
+    """A ragged layer of 1804 tiles, seven per CU, which takes the form of four waves a tile (the
+    sizes of test_block_parity take the one of eight): the block and the output layer, below a
+    coarser block or alone, against the oracle with the bar of test_block_parity (carried
+    through the output layer), and bit for bit the texels of a corner of it decoded as a layer of 380
+    tiles."""
+    import torch
+    W, H, w, h = 700, 650, 320, 300
+    nl = 2 if below else 1
+    d, wt = _decoder(W, H, nl, D, 81 + D, out_dim=out_dim, dev=gpu)
+    rng = np.random.default_rng(82)
+    feat = rng.uniform(0, 1, (H, W, D)).astype(np.float32)
+    feat[rng.random((H, W)) < 0.2] = 0
+    coarse = rng.uniform(-0.5, 1.5, (H // 2, W // 2, F)).astype(np.float16) if below else None
+
+    def run(dd, f, c, final):
+        c = None if c is None else torch.from_numpy(np.ascontiguousarray(c)).to(gpu)
+        return dd.block(0, torch.from_numpy(np.ascontiguousarray(f)).to(gpu), c,
+                        final=final).cpu().numpy()
+
+    got, img = run(d, feat, coarse, False), run(d, feat, coarse, True)
+    ref = dec.block(feat, coarse, wt["w"][0], wt["b"][0], fp16=True)
+    x = dec.r16(feat)
+    if below:
+        up = dec.r16(dec.upsample2(coarse, H, W))
+        x = np.concatenate([x, up], axis=2)
+    bar = _block_bar(np.abs(x), wt["w"][0], wt["b"][0], ref)
+    if below:
+        bar = bar + np.spacing(np.abs(up).astype(np.float16)).astype(np.float64)
+    bad = np.abs(got.astype(np.float64) - ref) > bar
+    assert not bad.any(), (int(bad.sum()), got[bad][:4], ref[bad][:4])
+    # the output: the block's bar through the 1x1 layer, and its 33 float32 additions
+    wo, bo = np.abs(wt["wo"].astype(np.float64)), np.abs(wt["bo"].astype(np.float64))
+    ibar = bar.max(axis=2, keepdims=True) * wo.sum(axis=0)
+    ibar = ibar + 66 * 2.0 ** -24 * (np.abs(ref) @ wo + bo)
+    assert np.all(np.abs(img - dec.output_layer(ref, wt["wo"], wt["bo"])) <= ibar)
+    # the corner's texels away from its own right and lower edges see the same neighbours
+    import paper_2401_06003_amd as tp
+    small = tp.Decoder(w, h, nl, D, wt, device=gpu)
+    part = None if coarse is None else coarse[:h // 2, :w // 2]
+    for final, whole in ((False, got), (True, img)):
+        corner = run(small, feat[:h, :w], part, final)
+        assert np.array_equal(corner[:h - 2, :w - 2], whole[:h - 2, :w - 2])
