@@ -714,7 +714,7 @@ __global__ __launch_bounds__(64) void k_binscan(const uint32_t* __restrict__ tot
 
 // Where the backward finds the rows of a point's entries: the positions of its first four, in slot
 // order, in one 16-byte record, of any others (a footprint across a tile corner) in a second table
-// that is only touched for such points, about one in fifty.  pv: view * points + point.  Writing
+// that is only touched for such points, about one in two hundred.  pv: view * points + point.  Writing
 // this is traffic the scatter is bound by: against one 32-byte record with a word for each of the
 // eight slots, 2M points scatter in 62 us instead of 68, 8M in 265 instead of 290, and the point
 // pass, which reads it, takes 68 us instead of 70 and 220 instead of 227.

@@ -127,3 +127,31 @@ def test_default_point_blocks_of_large_tables(gpu):
         del r
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+def _tile_entries(sc, tile_w):
+    """Entries of every point that writes a fragment: the tiles of its fragments."""
+    f = oracle.fragments(sc["points"], sc["cams"][0], sc["nlayers"])
+    touched = np.unique(np.stack([f["idx"], f["L"], f["i"] // tile_w, f["j"] // (256 // tile_w)], 1),
+                        axis=0)
+    return np.bincount(touched[:, 0])
+
+
+@pytest.mark.parametrize("n,D,tile_w", [(3000, 4, 8), (4096, 8, 16), (6000, 4, 16), (6000, 8, 8)])
+def test_points_on_tile_corners(gpu, n, D, tile_w):
+    """A third of the points within half a texel of a corner where four tiles of layer 0 and four
+    of layer 1 meet, so that hundreds have five to eight entries and use the second table of entry
+    positions; binned by one workgroup and by four passes.  (Random points do so only about once
+    in 200: in test_points_with_more_than_four_entries four to seven of all.)"""
+    import paper_2401_06003_amd as tp
+    sc = scenes.random_small(51, n=n, W=96, H=160, nlayers=4, D=D, s_lo=0.5, s_hi=8.0)
+    cam, p = sc["cams"][0], sc["points"]
+    rng = np.random.default_rng(52)
+    m = n // 3
+    step = (2 * tile_w, 512 // tile_w)  # corners common to layers 0 and 1
+    for k, c, f, size, s in (("x", "cx", "fx", 96, step[0]), ("y", "cy", "fy", 160, step[1])):
+        at = s * rng.integers(1, -(-size // s), m) + rng.uniform(-0.4, 0.4, m)
+        p[k][:m] = (at - float(cam[c])) * p["z"][:m] / float(cam[f])
+    per = _tile_entries(sc, tile_w)
+    assert (per > 4).sum() > 100 and (per == 8).sum() > 50, ((per > 4).sum(), (per == 8).sum())
+    _check(sc, gpu, tp.make_tuning(tile_w, 0, 0))
