@@ -3931,6 +3931,15 @@ trips_status side_by_side(bool in_line, hipStream_t st, F&& first, B&& beside, A
   return TRIPS_OK;
 }
 
+// Workgroups that find every work item of a call: at most E entries make at most E / (fine_e + 1)
+// tiles with items and E / item_e more items than such tiles.  (The capacity, a slot per tile and
+// more, is far above that for few points in many or large views, and a workgroup without an item
+// still waits for the LDS and wavefronts of a whole one: forward of 256 points in 16 views of
+// 1920x1080 478 us with a workgroup per slot, 409 with these.)
+uint32_t item_grid(const Layout& lay) {
+  return uint32_t(std::min<uint64_t>(lay.icap, lay.ecap / (lay.P.fine_e + 1) + lay.ecap / lay.P.item_e + 1));
+}
+
 // Largest tile count of layer L over the views (grid width of the per-layer passes).
 uint32_t layer_tiles_max(const Params& P, int L) {
   uint32_t m = 0;
@@ -4037,7 +4046,7 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
                               // workgroups beyond the item count exit at once
           StageTimer tm(ST_FWD_ITEMS, q);
           if (uint64_t(P.n) * uint64_t(P.V) <= SELECT_POINTS)
-            hipLaunchKernelGGL(k_fwd_select<D>, dim3(uint32_t(lay.icap)), dim3(FI_T), 0, q, P, info,
+            hipLaunchKernelGGL(k_fwd_select<D>, dim3(item_grid(lay)), dim3(FI_T), 0, q, P, info,
                                work, ent, pts.desc, pyr, npix, kkey, kgam, pcnt, pkey, pgam, X.bg,
                                X.alpha);
           else

@@ -155,3 +155,20 @@ def test_points_on_tile_corners(gpu, n, D, tile_w):
     per = _tile_entries(sc, tile_w)
     assert (per > 4).sum() > 100 and (per == 8).sum() > 50, ((per > 4).sum(), (per == 8).sum())
     _check(sc, gpu, tp.make_tuning(tile_w, 0, 0))
+
+
+@pytest.mark.parametrize("item", [0, 256])
+@pytest.mark.parametrize("n", [257, 1025])
+def test_as_many_items_as_entries_allow(gpu, n, item):
+    """Every point on a corner of four tiles in both of its layers: eight entries each, in eight
+    tiles of n entries, so that (n = 257, items of 256) one item fewer than a launch provides for
+    is in use."""
+    import paper_2401_06003_amd as tp
+    sc = scenes.random_small(53, n=n, W=64, H=64, nlayers=3, s_lo=1.1, s_hi=1.9)
+    cam, p = sc["cams"][0], sc["points"]
+    rng = np.random.default_rng(54)
+    for k, c, f in (("x", "cx", "fx"), ("y", "cy", "fy")):
+        p[k][:] = (32.0 + rng.uniform(-0.4, 0.4, n) - float(cam[c])) * p["z"] / float(cam[f])
+    assert (_tile_entries(sc, 16) == 8).all()
+    r = _check(sc, gpu, tp.make_tuning(16, 0, item))
+    assert (r.tile_stats()[0] == n).sum() == 8
