@@ -1110,12 +1110,26 @@ constexpr int FI_BINS = 64;
 constexpr uint32_t FI_RUN = 128;
 constexpr uint32_t FI_AHEAD = 2;
 static_assert(FI_CAP >= uint32_t(KEEP) * TP, "the kept lists of a tile fit");
-// Up to SELECT_POINTS (point, view) pairs the work items are too few to fill the chip, and the
-// forward lasts as long as its longest item: fwd_select, whose items are shorter, is the faster
-// one.  Above, it reads the entries three times where fwd_items reads them once.  Forward of
-// 1920x1080, 7 layers, fwd_items against fwd_select: 64k points 170 / 113 us, 500k 189 / 130,
-// 1M 196 / 162, 1.5M 233 / 225 (in Morton order 230 / 236), 2M 275 / 280 (Morton 262 / 310).
-constexpr uint64_t SELECT_POINTS = 1250000;
+// Which calls take fwd_select, by their (point, view) pairs (use_select).  Where the work items are
+// too few to fill the chip the forward lasts as long as its longest item, and fwd_select's are
+// shorter; where they are many it loses, reading the entries three times and fwd_items once.  Long
+// items come with points per pixel, so sparse calls leave earlier than dense ones; items of few
+// entries are few rounds of fwd_items however dense the call.  Forward by fwd_items / fwd_select,
+// clusters (points uniform over the image in brackets), us:
+//   pairs  1 x 2560x1440  1 x 1920x1080  1 x 640x480    4 x 1280x720   16 x 640x480
+//   300k   188 / 133      182 / 130      186 / 126      179 / 134      163 / 149
+//          (136 / 140)    (162 / 115)    (175 / 110)    (134 / 134)    (156 / 154)
+//   700k   197 / 169      182 / 135      397 / 227      183 / 155      183 / 177
+//          (182 / 191)    (185 / 149)    (378 / 172)    (165 / 183)    (175 / 172)
+//   900k   202 / 183      191 / 157      401 / 237      184 / 174      185 / 194
+//          (193 / 207)    (186 / 167)    (372 / 174)    (178 / 195)    (193 / 203)
+//   1.2M   234 / 234      214 / 199      410 / 236      211 / 215      226 / 238
+//          (252 / 265)    (212 / 208)    (386 / 202)    (226 / 233)    (247 / 266)
+// Items of 512 entries, 640x480, 600k points: 204 / 210, 100k 110 / 106; of 1024, 1M points at
+// 1920x1080 200 / 210, 100k at 256x256 109 / 97; of 2048, 600k 140 / 133.
+constexpr uint64_t SELECT_POINTS = 700000;
+constexpr uint64_t SELECT_DENSE = 1250000;     // ... with at least half a point per pixel
+constexpr uint64_t SELECT_PER_ENTRY = 300;     // ... and at most this many per entry of an item
 
 // Compare-exchange of (key, gamma) pairs: afterwards a holds the smaller key.
 __device__ __forceinline__ void cswap(uint64_t& ka, float& ga, uint64_t& kb, float& gb) {
@@ -1335,7 +1349,7 @@ __global__ __launch_bounds__(256) void k_fwd_items(
   }
 }
 
-// fwd_select: the work items again, one workgroup each, for clouds of few points (SELECT_POINTS).
+// fwd_select: the work items again, one workgroup each, for clouds of few points (use_select).
 // Of a texel's fragments only the 16 front-most are wanted, so the item's entries are streamed
 // instead of being sorted:
 //  - the first pass counts every fragment in its texel's depth bin (FI_BINS bins over the
@@ -3940,6 +3954,15 @@ uint32_t item_grid(const Layout& lay) {
   return uint32_t(std::min<uint64_t>(lay.icap, lay.ecap / (lay.P.fine_e + 1) + lay.ecap / lay.P.item_e + 1));
 }
 
+// Does the forward's item kernel select (fwd_select) or sort (fwd_items)?
+bool use_select(const Params& P) {
+  const uint64_t pairs = uint64_t(P.n) * uint64_t(P.V);
+  uint64_t px = 0;
+  for (int v = 0; v < P.V; ++v) px += uint64_t(P.view[v].W) * uint64_t(P.view[v].H);
+  return pairs <= SELECT_PER_ENTRY * P.item_e &&
+         (pairs <= SELECT_POINTS || (pairs <= SELECT_DENSE && 2 * pairs >= px));
+}
+
 // Largest tile count of layer L over the views (grid width of the per-layer passes).
 uint32_t layer_tiles_max(const Params& P, int L) {
   uint32_t m = 0;
@@ -4045,7 +4068,7 @@ trips_status launch_forward(const Layout& lay, const trips_points& pts, float* p
         [&](hipStream_t q) {  // one workgroup per work item (the longer path, enqueued first);
                               // workgroups beyond the item count exit at once
           StageTimer tm(ST_FWD_ITEMS, q);
-          if (uint64_t(P.n) * uint64_t(P.V) <= SELECT_POINTS)
+          if (use_select(P))
             hipLaunchKernelGGL(k_fwd_select<D>, dim3(item_grid(lay)), dim3(FI_T), 0, q, P, info,
                                work, ent, pts.desc, pyr, npix, kkey, kgam, pcnt, pkey, pgam, X.bg,
                                X.alpha);

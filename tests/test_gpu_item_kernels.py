@@ -1,5 +1,5 @@
-"""The item kernels of the forward give the same texels.  Calls of up to 1.25M (point, view) pairs
-select a tile's lists by counting (k_fwd_select), larger ones sort in rounds (k_fwd_items): every
+"""The item kernels of the forward give the same texels.  Calls of few (point, view) pairs select
+a tile's lists by counting (k_fwd_select), larger ones sort in rounds (k_fwd_items): every
 small scene here is rendered twice, alone and followed by points behind the camera that raise the
 count, so the same lists come from both.  Against each other bit for bit, and the larger call
 against the oracle with the tolerances of gpu_util."""
