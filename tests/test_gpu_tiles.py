@@ -172,3 +172,37 @@ def test_as_many_items_as_entries_allow(gpu, n, item):
     assert (_tile_entries(sc, 16) == 8).all()
     r = _check(sc, gpu, tp.make_tuning(16, 0, item))
     assert (r.tile_stats()[0] == n).sum() == 8
+
+
+@pytest.mark.parametrize("n,D,tile_w,item", [(150000, 4, 16, 256), (300000, 8, 8, 500),
+                                             (200000, 4, 64, 300)])
+def test_backward_of_joined_items(gpu, n, D, tile_w, item):
+    """More small items than fit the chip at once: the backward takes those of a tile in runs, the
+    last of them short; with a background gradient, which one run of a tile writes."""
+    import torch
+    import paper_2401_06003_amd as tp
+    sc = scenes.random_small(55, n=n, W=150, H=99, nlayers=4, D=D, s_lo=0.4, s_hi=14.0)
+    cam, nl = sc["cams"][0], sc["nlayers"]
+    t = to_device(sc["points"], gpu)
+    args = [t[k] for k in PARAMS]
+    got = []
+    for it in (item, 65536):
+        r = tp.Renderer([cam], nl, D, n, tuning=tp.make_tuning(tile_w, 0, it), device=gpu)
+        P = r.texels
+        rng = np.random.default_rng(56)
+        bg = rng.uniform(0.0, 1.0, (P, D)).astype(np.float32)
+        G = scenes.upstream_gradient(57, P * D).reshape(P, D).astype(np.float32)
+        d_bg, d_G = (torch.from_numpy(a.reshape(-1)).to(gpu) for a in (bg, G))
+        gbg = torch.zeros(P * D, device=gpu)
+        r.forward(*args, background=d_bg)
+        if it == item:
+            assert r.stats()["items"] > r.stats()["bins"] + 512
+        got.append(r.backward(*args, d_G, background=d_bg, grad_background=gbg) + [gbg])
+    for a, b in zip(*got):  # whole tiles and cut ones
+        assert torch.equal(a, b)
+    want = oracle.backward_ex(sc["points"], cam, nl, G.astype(np.float64),
+                              background=bg.astype(np.float64))
+    for k, o in zip(PARAMS + ("bg",), got[0]):
+        g = o.cpu().numpy().astype(np.float64)
+        w = want["gbg"] if k == "bg" else want[GRAD_KEY[k]]
+        grad_close(g, w.reshape(g.shape), k)
