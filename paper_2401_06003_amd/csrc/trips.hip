@@ -2063,7 +2063,10 @@ __device__ __forceinline__ float2 blend_adjoint_step(float Tm, float gam, float 
 // A corner is kept iff its key is not above the texel's last kept key; a wavefront collects the
 // entries that have such a corner until every lane holds one.  The lists are in depth order, so a
 // kept corner's slot is found by bisection of the texel's depths in LDS (four reads instead of a
-// comparison with all 16 point ids); where a list holds equal depths the stored keys tell.  An
+// comparison with all 16 point ids); where a list holds equal depths, of the depths and the stored
+// keys' indices, the four corners at once (rolled: unrolled it takes 6 registers more, and with them
+// 5% of a call without equal depths; the indices in LDS cost as much, for the room of fine tiles'
+// workgroups beside these).  An
 // entry without a kept corner writes no row, only its mark in `kept`: a byte per entry, written
 // here or by bwd_fine for every entry of the call, so nothing is cleared first and `saved` stays
 // as the forward left it.
@@ -2238,7 +2241,7 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
   // the row of an entry with kept corners (bit mask pm & 15, local texel of corner 0 pm >> 4)
   auto write_row = [&](uint32_t e, int pm, float u, float v, uint32_t z, uint32_t idx) {
     const float fu = u - floorf(u), fv = v - floorf(v);
-    uint32_t pos[4];
+    uint32_t pos[4], ties = 0;  // (corners in lists with equal depths)
     float2 st[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -2247,9 +2250,28 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
       uint32_t m = 0;
 #pragma unroll
       for (uint32_t st2 = KEEP / 2; st2 >= 1; st2 /= 2) m += s_z[m + st2 - 1][p] < z ? st2 : 0u;
-      if (((pm >> q) & 1) && (s_last[p].x & TIE))  // equal depths in the list: the slot with
-        while (m < KEEP - 1 && uint32_t(kkey[(size_t(b) * KEEP + m) * TP + p]) != idx) ++m;
       pos[q] = m * TP + p;
+      ties |= ((pm >> q) & 1) && (s_last[p].x & TIE) ? 1u << q : 0u;
+    }
+    if (ties != 0) {  // again by depth and index, the four corners together
+      const uint64_t* kl = kkey + size_t(b) * KEEP * TP;
+      uint32_t at[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) at[q] = pos[q] % TP;
+#pragma unroll 1
+      for (uint32_t st2 = KEEP / 2; st2 >= 1; st2 /= 2) {
+        uint32_t zm[4], id[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {  // (slot 0 of the texel where the index is not needed)
+          const uint32_t o = at[q] + (st2 - 1) * TP;
+          zm[q] = s_z[0][o];
+          id[q] = uint32_t(kl[zm[q] == z ? o : o % TP]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) at[q] += zm[q] < z || (zm[q] == z && id[q] < idx) ? st2 * TP : 0u;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) pos[q] = (ties >> q) & 1u ? at[q] : pos[q];
     }
     float itau[4][INC ? D : 1];
 #pragma unroll
