@@ -402,9 +402,11 @@ class Plan:
             self.h = None
 
 
-# Launch shapes tried by default: tile width x points per binning block x entries per item.
-DEFAULT_CANDIDATES = [(tw, pb, ie) for tw in (8, 16, 32) for pb in (4096, 8192)
-                      for ie in (4096, 8192, 16384)]
+# Launch shapes tried by default: the library's own choice (zeros; blocks and items that follow the
+# workload, which none of the others may equal), then tile width x points per binning block x
+# entries per item.
+DEFAULT_CANDIDATES = [(0, 0, 0)] + [(tw, pb, ie) for tw in (8, 16, 32) for pb in (4096, 8192)
+                                    for ie in (4096, 8192, 16384)]
 
 
 def autotune(cams, num_layers, desc_dim, x, y, z, sw, alpha, desc, candidates=None, reps=3,
@@ -413,7 +415,8 @@ def autotune(cams, num_layers, desc_dim, x, y, z, sw, alpha, desc, candidates=No
     (trips_autotune: forward + backward timed with HIP events per candidate).
 
     Results are cached in a JSON file (cache_path, default $TRIPS_TUNE_CACHE if set) keyed
-    by the device name and the workload's shape.  Returns (Tuning, {candidate: ms})."""
+    by the device name and the workload's shape.  Returns (Tuning, {candidate: ms}); a zero
+    stands for the library's default."""
     import json
     if isinstance(cams, dict):
         cams = [cams]

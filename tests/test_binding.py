@@ -82,3 +82,12 @@ def test_separate_buffers_do_not_interfere(monkeypatch):
     out = tp.render(*a, r)
     tp.render(*a, r2)
     out.sum().backward()
+
+
+def test_autotuner_tries_the_default_shape():
+    """The library's own choice of launch shape is among the candidates tried by default: it
+    follows the workload (blocks of up to 32768 points, items of up to 32768 entries), so a search
+    without it can return a slower one."""
+    import paper_2401_06003_amd as tp
+    assert (0, 0, 0) in tp.DEFAULT_CANDIDATES
+    assert len(set(tp.DEFAULT_CANDIDATES)) == len(tp.DEFAULT_CANDIDATES)

@@ -96,3 +96,20 @@ def test_autotuner_picks_a_candidate(gpu, tmp_path):
     again, _ = tp.autotune(sc["cams"], sc["nlayers"], sc["D"], *[t[k] for k in PARAMS],
                            candidates=cands, reps=2, cache_path=cache, device=gpu)  # from cache
     assert (again.tile_w, again.points_per_block, again.item_entries) == chosen
+
+
+def test_autotuner_is_no_slower_than_the_defaults(gpu):
+    """With the candidates tried by default, the default shape among them."""
+    import torch
+    import paper_2401_06003_amd as tp
+    sc = scenes.unit_cube(9, n=5000, W=160, H=120, nlayers=5)
+    t = to_device(sc["points"], gpu)
+    args = [t[k] for k in PARAMS]
+    best, ms = tp.autotune(sc["cams"], sc["nlayers"], sc["D"], *args, reps=2, device=gpu)
+    chosen = (best.tile_w, best.points_per_block, best.item_entries)
+    assert set(ms) == set(tp.DEFAULT_CANDIDATES)
+    assert ms[chosen] <= ms[(0, 0, 0)]
+    n = len(sc["points"]["x"])
+    a = tp.Renderer(sc["cams"], sc["nlayers"], sc["D"], n, tuning=best, device=gpu).forward(*args)
+    b = tp.Renderer(sc["cams"], sc["nlayers"], sc["D"], n, device=gpu).forward(*args)
+    assert torch.equal(a, b)
