@@ -3967,9 +3967,17 @@ trips_status side_stream(SideStream*& out) {
 constexpr uint64_t IN_LINE_FWD = 4096, IN_LINE_BWD = 16384;  // (point, view) pairs
 template <class F, class B, class A>
 trips_status side_by_side(bool in_line, hipStream_t st, F&& first, B&& beside, A&& after) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (in_line) TRIPS_HIP(hipStreamIsCapturing(st, &cs));
-  if (in_line && cs == hipStreamCaptureStatusNone) {
+  // (the null stream is never captured, but asking about it fails while another thread captures a
+  // stream that waits for it; where the answer is not known the forked form is right either way)
+  if (in_line && st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+      (void)hipGetLastError();
+      in_line = false;
+    }
+    if (cs != hipStreamCaptureStatusNone) in_line = false;
+  }
+  if (in_line) {
     first(st);
     beside(st);
     after(st);

@@ -73,3 +73,54 @@ def test_one_workgroup_binning_up_to_11264_tiles(gpu, n):
     for a, b in zip(*got):
         assert torch.equal(a, b)
     assert float(got[0][0].abs().max()) > 0
+
+
+def test_small_calls_while_another_thread_captures(gpu):
+    """A call of a few points on the null stream, which asks whether its stream is being captured,
+    is accepted while another thread captures a stream of its own, as a larger call is."""
+    import ctypes
+    import threading
+
+    import torch
+    sc = scenes.random_small(120, n=300, W=61, H=45, nlayers=4)
+    big = scenes.random_small(121, n=30000, W=61, H=45, nlayers=4)
+    calls = []
+    for s in (sc, big):
+        r = renderer(s, gpu)
+        t = to_device(s["points"], gpu)
+        args = [t[k] for k in PARAMS]
+        out = r.forward(*args)
+        G = torch.ones_like(out)
+        want = [out.clone()] + [g.clone() for g in r.backward(*args, G)]
+        outs = [torch.empty_like(g) for g in want[1:]]
+        calls.append((r, args, out, G, outs, want))
+    torch.cuda.synchronize()
+    assert torch.cuda.current_stream().cuda_stream == 0
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    stream, graph = ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipStreamCreate(ctypes.byref(stream)) == 0
+    begun, finish, codes = threading.Event(), threading.Event(), []
+
+    def capture():
+        codes.append(hip.hipStreamBeginCapture(stream, 1))  # hipStreamCaptureModeThreadLocal
+        begun.set()
+        finish.wait(30)
+        codes.append(hip.hipStreamEndCapture(stream, ctypes.byref(graph)))
+
+    th = threading.Thread(target=capture)
+    th.start()
+    assert begun.wait(30)
+    try:
+        for r, args, out, G, outs, want in calls:
+            r.forward(*args, out=out)
+            r.backward(*args, G, outs=outs)
+    finally:
+        finish.set()
+        th.join()
+    torch.cuda.synchronize()
+    assert codes == [0, 0]
+    assert hip.hipGraphDestroy(graph) == 0 and hip.hipStreamDestroy(stream) == 0
+    for r, args, out, G, outs, want in calls:
+        for a, b in zip([out] + outs, want):
+            assert torch.equal(a, b)
