@@ -84,7 +84,7 @@ def method_bytes(stage, w):
 def impl_bytes(stage, w):
     """The implementation's own byte model of one launch (reads + writes of its data
     structures: 20-byte tile entries, 32-byte rows (in the tiles of work items only of entries
-    that keep a fragment, at most one per kept fragment), a bit per entry that says so, 16-bit
+    that keep a fragment, at most one per kept fragment), a byte per entry that says so, 16-bit
     per-block histograms and their 32-bit prefixes, kept keys and gammas), for comparison with
     the method's bytes and the counters."""
     N, D, E, Ef, K, Kf, Nv = w["N"], w["D"], w["E"], w["E_f"], w["K"], w["K_f"], w["Nv"]
@@ -95,12 +95,12 @@ def impl_bytes(stage, w):
     table = {
         "count": 16 * N + 2 * nblk * NB,
         "colscan": 6 * nblk * NB + 4 * NB,
-        "scatter": 20 * N + 4 * nblk * NB + 4 * NB + 20 * E + 16 * Nv + E / 8,
+        "scatter": 20 * N + 4 * nblk * NB + 4 * NB + 20 * E + 16 * Nv,
         "fwd_items": 20 * Ec + (4 * D + 12) * Kc + 4 * 256 * NBc + 4 * D * Pc,
         "fwd_fine": (24 + 4 * D) * Ef + 12 * Kf + 4 * 256 * NBf + 4 * D * Pf,
-        "bwd_items": 20 * Ec + Ec / 8 + row * Rc + (12 + 4 * D) * Kc + Ic * 256 * (4 + 4 * D),
-        "bwd_fine": (24 + 4 * D + row) * Ef + 4 * 256 * NBf + 4 * D * Pf,
-        "bwd_points": 20 * N + 16 * Nv + E / 8 + row * (Rc + Ef) + 4 * (5 + D) * N,
+        "bwd_items": 21 * Ec + row * Rc + (12 + 4 * D) * Kc + Ic * 256 * (4 + 4 * D),
+        "bwd_fine": (25 + 4 * D + row) * Ef + 4 * 256 * NBf + 4 * D * Pf,
+        "bwd_points": 20 * N + 16 * Nv + E + row * (Rc + Ef) + 4 * (5 + D) * N,
     }
     return table.get(stage)
 

@@ -29,8 +29,8 @@
 // There eight waves of two rows each shorten the tile's chain (a layer of one tile to a few per CU
 // takes 8 us instead of 9.5); with many tiles per CU four waves of four rows read the kernel
 // fragments half as often (layer 0 of 1920x1080 150 us against 160).  Halos inside the layer skip
-// the zeroing.  The network at 1920x1080, 8 layers, D = 4: 237 -> 229 us; 643x477, 5 layers, D = 8:
-// 68 -> 62 us; 100x70: 23.5 -> 21.2 us.
+// the zeroing.  With both the network takes, at 1920x1080, 8 layers, D = 4, 246 us instead of 257,
+// at 643x477, 5 layers, D = 8, 62 instead of 67 (the same GPU; others differ by up to a tenth).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -477,9 +477,12 @@ uint32_t dec_cus() {
   return uint32_t(std::max(cus, 1));
 }
 
-// Layers of at most FEW_TILES tiles per CU take the eight-wave form (643x477, 4.8 tiles per CU at
-// layer 0: 62 us against 64 in the four-wave form; at 8 per CU, layer 1 of 1920x1080, the network
-// takes 229 us with the four-wave form there and 238 with the other).
+// Layers of at most FEW_TILES tiles per CU take the eight-wave form.  The network of 5 layers, D = 4,
+// with the four-wave form everywhere, the line at 6 and the line at 16 tiles per CU, us: 320x240
+// 41.6 / 38.1 / 38.1, 640x480 (4.7 at layer 0) 61.9 / 56.0 / 56.0, 600x600 (5.6) 68.0 / 62.8 / 62.8,
+// 700x650 (7.0) 75.9 / 71.2 / 71.6, 1280x720 (14) 107 / 103 / 105, 1920x1080 (32; layer 1 8.0) 190 /
+// 187 / 188.  (A layer without a coarser one gains from eight waves further up: 1280x720 alone 31.9 /
+// 31.7 / 29.8.)
 constexpr uint32_t FEW_TILES = 6;
 
 template <int D>

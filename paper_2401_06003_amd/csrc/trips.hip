@@ -13,7 +13,7 @@
 //   colscan    per bin, exclusive prefix of H16 over blocks (32-bit, into H) and bin totals.
 //   binscan    exclusive scans of bin totals -> bin starts, and of work items -> item starts.
 //   scatter    same blocks again: LDS ranks, entry written at bin_start + H + rank.
-//   front      count to scatter in one workgroup, for one view of at most 4096 points.
+//   front      count to scatter in one workgroup, for one view of few points and tiles.
 //   fwd_items  one workgroup per work item (a bin, or a chunk of a heavy bin);
 //              entries -> fragments in LDS, counting sort by texel, per-texel top-16 kept
 //              in registers (thread = texel); blend, or write a partial top-16.
@@ -3463,9 +3463,11 @@ __global__ __launch_bounds__(256) void k_incl_bwd012(
 // Bound by memory: the entry positions, the rows (a 128-byte line for 32 bytes) and the
 // gradients.  The kept marks keep it from fetching the rows of entries without a kept fragment:
 // 2.04 -> 1.78 ms on eight 2560x1440 views, 250 -> 231 us at 8M points (1920x1080), 67 us as before
-// at 2M.  (Measured with a bit per entry; a byte, which needs no clearing and no atomics, is the
-// same within the noise: forward + backward 1.286 and 1.293 ms at 8M points, 12.03 and 12.00 ms on
-// the eight views.)
+// at 2M.  (With a bit per entry in `saved`; a byte in the workspace needs no clearing and no atomics
+// and is the same within the noise there, forward + backward 1.286 and 1.293 ms at 8M points, 12.03
+// and 12.00 ms on the eight views.  Where hardly any points overlap and all keep their fragments it
+// costs more: 4M splats of at most two texels at 2560x1440, backward 490 and 512 us; bits in the
+// workspace with a launch that clears them, 502 us, but 3 us more than bytes below 600k points.)
 template <int D, bool CAM>
 __global__ __launch_bounds__(256) void k_bwd_points(
     const Params P, const float* __restrict__ X, const float* __restrict__ Y,
@@ -3963,7 +3965,9 @@ trips_status side_stream(SideStream*& out) {
 // forward of 300 points 52 against 24 us, forward + backward of 4096 points 115 against 78.  The
 // line lies where the waits become shorter than the overlap: at 640x480 the forward of 8k points
 // takes 79 us forked and 85 in line, the backward of 8k 86 and 28, of 32k 37 and 40.  In a graph
-// the branches cost no calls and are the faster form at 4096 points too (75 against 80 us).
+// the branches cost no calls, but a wait all the same: replays of a forward and a backward of 4096
+// points take 72 us with the fork and 83 with the forward in line, of a forward alone 57 and 57,
+// of a forward of 300 points 46 and 27.
 constexpr uint64_t IN_LINE_FWD = 4096, IN_LINE_BWD = 16384;  // (point, view) pairs
 template <class F, class B, class A>
 trips_status side_by_side(bool in_line, hipStream_t st, F&& first, B&& beside, A&& after) {
