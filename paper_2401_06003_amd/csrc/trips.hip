@@ -2079,9 +2079,10 @@ __device__ __forceinline__ float2 blend_adjoint_step(float Tm, float gam, float 
 // entries that have such a corner until every lane holds one.  The lists are in depth order, so a
 // kept corner's slot is found by bisection of the texel's depths in LDS (four reads instead of a
 // comparison with all 16 point ids); where a list holds equal depths, of the depths and the stored
-// keys' indices, the four corners at once (rolled: unrolled it takes 6 registers more, and with them
-// 5% of a call without equal depths; the indices in LDS cost as much, for the room of fine tiles'
-// workgroups beside these).  An
+// keys' indices, the four corners at once (a frontal plane of 300k points at 640x480, backward: 50 us,
+// with the keys walked corner by corner 82.  The loop stays rolled: unrolled it takes 6 registers
+// more, and with them 5% of a call without equal depths; the indices in LDS cost as much, for the
+// room of fine tiles' workgroups beside these).  An
 // entry without a kept corner writes no row, only its mark in `kept`: a byte per entry, written
 // here or by bwd_fine for every entry of the call, so nothing is cleared first and `saved` stays
 // as the forward left it.
@@ -2253,11 +2254,14 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
     }
   }
   __syncthreads();
-  // the row of an entry with kept corners (bit mask pm & 15, local texel of corner 0 pm >> 4)
+  // the row of an entry with kept corners (bit mask pm & 15, local texel of corner 0 pm >> 4, bit 30
+  // of pm flipped if one of their lists holds equal depths)
   auto write_row = [&](uint32_t e, int pm, float u, float v, uint32_t z, uint32_t idx) {
     const float fu = u - floorf(u), fv = v - floorf(v);
-    uint32_t pos[4], ties = 0;  // (corners in lists with equal depths)
+    uint32_t pos[4];
     float2 st[4];
+    const bool ties = ((pm >> 30) ^ (pm >> 31)) & 1;  // (some list holds equal depths)
+    pm = int(uint32_t(pm) << 2) >> 2;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       // (a corner that is not kept bisects some texel of the tile and is dropped)
@@ -2266,27 +2270,23 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
 #pragma unroll
       for (uint32_t st2 = KEEP / 2; st2 >= 1; st2 /= 2) m += s_z[m + st2 - 1][p] < z ? st2 : 0u;
       pos[q] = m * TP + p;
-      ties |= ((pm >> q) & 1) && (s_last[p].x & TIE) ? 1u << q : 0u;
     }
-    if (ties != 0) {  // again by depth and index, the four corners together
+    if (ties) {  // again by depth and index, the four corners together
       const uint64_t* kl = kkey + size_t(b) * KEEP * TP;
-      uint32_t at[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) at[q] = pos[q] % TP;
+      for (int q = 0; q < 4; ++q) pos[q] %= TP;
 #pragma unroll 1
       for (uint32_t st2 = KEEP / 2; st2 >= 1; st2 /= 2) {
         uint32_t zm[4], id[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {  // (slot 0 of the texel where the index is not needed)
-          const uint32_t o = at[q] + (st2 - 1) * TP;
+          const uint32_t o = pos[q] + (st2 - 1) * TP;
           zm[q] = s_z[0][o];
           id[q] = uint32_t(kl[zm[q] == z ? o : o % TP]);
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) at[q] += zm[q] < z || (zm[q] == z && id[q] < idx) ? st2 * TP : 0u;
+        for (int q = 0; q < 4; ++q) pos[q] += zm[q] < z || (zm[q] == z && id[q] < idx) ? st2 * TP : 0u;
       }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) pos[q] = (ties >> q) & 1u ? at[q] : pos[q];
     }
     float itau[4][INC ? D : 1];
 #pragma unroll
@@ -2327,6 +2327,8 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
   // has one for every lane: about a quarter of the entries keep a fragment, and their rows take
   // most of the work.
   const uint32_t lane = t & 63;
+  // (a store of every lane, which no wait has to allow for being skipped)
+  const uint32_t no_entry = uint32_t(8 * P.n * P.V);
   uint32_t waiting = 0;
   uint32_t we = 0, wz = 0, wid = 0;
   int wpm = 0;
@@ -2345,15 +2347,18 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
       const int pa = eh < e1 ? tile_corners(tg, en[h].u, en[h].v, fu, fv) : 0;
       // kept: not behind the texel's last kept fragment
       int pm = pa & ~15;
+      uint32_t tie = 0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const uint2 last = s_last[uint32_t((pa >> 4) + (q & 1) + ((q >> 1) << P.ltw)) & (TP - 1)];
         const uint32_t lz = last.x & ~TIE;
         const bool on = ((pa >> q) & 1) && (en[h].zbits < lz || (en[h].zbits == lz && en[h].idx <= last.y));
         pm |= int(on) << q;
+        tie |= on ? last.x : 0u;
       }
+      pm ^= int(tie >> 31) << 30;  // (bits 29 to 31 are the sign otherwise)
       const bool any = (pm & 15) != 0;
-      if (eh < e1) kept[eh] = any ? 1 : 0;
+      kept[eh < e1 ? eh : no_entry] = any ? 1 : 0;
       const uint64_t bits = __ballot(any);
       if (bits == 0) continue;  // (uniform)
       // the entries with kept corners move to the lanes from `waiting` on, the others behind them
@@ -3463,11 +3468,12 @@ __global__ __launch_bounds__(256) void k_incl_bwd012(
 // Bound by memory: the entry positions, the rows (a 128-byte line for 32 bytes) and the
 // gradients.  The kept marks keep it from fetching the rows of entries without a kept fragment:
 // 2.04 -> 1.78 ms on eight 2560x1440 views, 250 -> 231 us at 8M points (1920x1080), 67 us as before
-// at 2M.  (With a bit per entry in `saved`; a byte in the workspace needs no clearing and no atomics
-// and is the same within the noise there, forward + backward 1.286 and 1.293 ms at 8M points, 12.03
-// and 12.00 ms on the eight views.  Where hardly any points overlap and all keep their fragments it
-// costs more: 4M splats of at most two texels at 2560x1440, backward 490 and 512 us; bits in the
-// workspace with a launch that clears them, 502 us, but 3 us more than bytes below 600k points.)
+// at 2M.  They were a bit per entry in `saved`; a byte in the workspace needs no clearing and no
+// atomics, but is more memory to gather from: backward of clusters of 8M points 486 us both ways, of
+// 2M 166 with bits and 163 with bytes; where hardly any points overlap and nearly all entries are
+// kept, 4M splats of at most two texels at 2560x1440, 490 and 501, 1.2M at 1920x1080 117 and 123.
+// (Bits in the workspace and a launch that clears them: 3 us more than bytes below 600k points,
+// level at 2.5M.)
 template <int D, bool CAM>
 __global__ __launch_bounds__(256) void k_bwd_points(
     const Params P, const float* __restrict__ X, const float* __restrict__ Y,
@@ -3858,7 +3864,7 @@ trips_status make_layout(const trips_config* cfg, const trips_camera* cams, int3
   // backward scratch reuses the same bytes
   o = scratch;
   lay.w_rows = take(size_t(views) * NSLOT * size_t(n) * (4 + P.D) * 4);
-  lay.w_kept = take(size_t(lay.ecap));  // a byte per entry: has a kept fragment
+  lay.w_kept = take(size_t(lay.ecap) + 1);  // a byte per entry: has a kept fragment; one for none
   lay.w_cam = take(size_t((n + 255) / 256) * size_t(views) * 16 * 4);
   lay.w_itot = take(inc * NB * TP * KEEP * size_t(1 + P.D) * 4);
   lay.w_iup = take(inc * NB * TP * KEEP * size_t(1 + P.D) * 4);
