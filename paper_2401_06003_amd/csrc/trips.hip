@@ -62,9 +62,9 @@ constexpr uint32_t BWD_SPLIT = 2;    // with coarser-layer inclusion
 constexpr uint32_t BWD_GRID = 2048;  // else: workgroups of a launch, at most
 // ... and every one forms the blend adjoint of its item's tile, so that a tile's items of fewer
 // entries than BWD_JOIN are taken several at a time where the items are more than the workgroups
-// that fit the chip.  Backward at 640x480, 600k points, items of 256 entries, one by one
-// and joined: 121 / 87 us, of 512 88 / 66, of 2048 66 / 63; 1M points at 1920x1080, 256: 215 / 150,
-// 1024: 140 / 126; 4096 points (60 items), 256: 20 one by one, 24 joined.
+// that fit the chip.  Backward at 640x480, 600k points, items of 256 entries, one by one and joined:
+// 121 / 87 us, of 512 88 / 66, of 2048 66 / 63; 1M points at 1920x1080, 256: 215 / 150, 1024:
+// 140 / 126; 4096 points (60 items), 256: 20 one by one, 24 joined.
 constexpr uint32_t BWD_FILL = 512;
 constexpr uint32_t BWD_JOIN = 8192;
 // Workgroups are dealt to the chip's 8 dies (XCDs, each with its own L2) in turn by index;
@@ -721,10 +721,10 @@ __global__ __launch_bounds__(64) void k_binscan(const uint32_t* __restrict__ tot
 
 // Where the backward finds the rows of a point's entries: the positions of its first four, in slot
 // order, in one 16-byte record, of any others (a footprint across a tile corner) in a second table
-// that is only touched for such points, about one in two hundred.  pv: view * points + point.  Writing
-// this is traffic the scatter is bound by: against one 32-byte record with a word for each of the
-// eight slots, 2M points scatter in 62 us instead of 68, 8M in 265 instead of 290, and the point
-// pass, which reads it, takes 68 us instead of 70 and 220 instead of 227.
+// that is only touched for such points, about one in two hundred.  pv: view * points + point.
+// Writing this is traffic the scatter is bound by: against one 32-byte record with a word for each
+// of the eight slots, 2M points scatter in 62 us instead of 68, 8M in 265 instead of 290, and the
+// point pass, which reads it, takes 68 us instead of 70 and 220 instead of 227.
 __device__ __forceinline__ void write_epos(uint32_t* __restrict__ epos, const Params& P, size_t pv,
                                            const uint32_t (&er)[NSLOT], uint32_t ne) {
   uint4* ep4 = reinterpret_cast<uint4*>(epos);
@@ -2079,13 +2079,12 @@ __device__ __forceinline__ float2 blend_adjoint_step(float Tm, float gam, float 
 // entries that have such a corner until every lane holds one.  The lists are in depth order, so a
 // kept corner's slot is found by bisection of the texel's depths in LDS (four reads instead of a
 // comparison with all 16 point ids); where a list holds equal depths, of the depths and the stored
-// keys' indices, the four corners at once (a frontal plane of 300k points at 640x480, backward: 50 us,
-// with the keys walked corner by corner 82.  The loop stays rolled: unrolled it takes 6 registers
-// more, and with them 5% of a call without equal depths; the indices in LDS cost as much, for the
-// room of fine tiles' workgroups beside these).  An
-// entry without a kept corner writes no row, only its mark in `kept`: a byte per entry, written
-// here or by bwd_fine for every entry of the call, so nothing is cleared first and `saved` stays
-// as the forward left it.
+// keys' indices, the four corners at once (a frontal plane of 300k points at 640x480, backward:
+// 50 us, with the keys walked corner by corner 82.  The loop stays rolled: unrolled it takes 6
+// registers more, and with them 5% of a call without equal depths; the indices in LDS cost as much,
+// for the room of fine tiles' workgroups beside these).  An entry without a kept corner writes no
+// row, only its mark in `kept`: a byte per entry, written here or by bwd_fine for every entry of the
+// call, so nothing is cleared first and `saved` stays as the forward left it.
 // With coarser-layer inclusion (INC) the kept own fragments are those the blended list took
 // (a prefix of the own list), and each one's totals (dL/dgamma, tau part) are read from
 // itot instead of being formed from the blend adjoint and G.
@@ -2281,7 +2280,7 @@ __global__ __launch_bounds__(T, INC ? 2 : 4) void k_bwd_items(
 #pragma unroll
         for (int q = 0; q < 4; ++q) {  // (slot 0 of the texel where the index is not needed)
           const uint32_t o = pos[q] + (st2 - 1) * TP;
-          zm[q] = s_z[0][o];
+          zm[q] = s_z[o / TP][o % TP];
           id[q] = uint32_t(kl[zm[q] == z ? o : o % TP]);
         }
 #pragma unroll
